@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, const Step* __res
         }
       }
       if (first || changed) Wout[node] = cur;
-      if (changed && w0 < inf_t<T>()) m = double(w0) - double(cur);
+      if (changed && w0 < inf_t<T>()) m = fmax(m, double(w0) - double(cur));
       if (carry && !(flags & kLast) && (first || changed)) {
         cy.sel[node] = sl;
         cy.soff[node] = so;

@@ -175,6 +175,19 @@ def test_grid_every_hull_path_on_random_values(lib, kind, n):
                                                                                        len(differ)))
 
 
+def test_grid_decrease_is_the_maximum_over_all_nodes(lib):
+    """The maximal decrease of an iteration on a mesh of more nodes than the pick launch has
+    threads (each thread visits several nodes): the largest of W^k - W^{k+1}, exactly."""
+    r1, h, torch = lib
+    n = (60, 27, 27, 61)
+    g = r1.grid(2, n, (0.5, -0.2, -0.3, 0.7), 0.05)
+    W0 = torch.tensor(np.random.default_rng(71).normal(size=r1.grid_size(g)), dtype=torch.float64, device="cuda")
+    W0[5] = 30.0                                      # the largest decrease, early in its thread's nodes
+    W = W0.clone()
+    hist = h.grid_laminate(g, r1.grid_r11(2), W, k_max=1, tol=0.0)
+    assert hist[0] == float((W0 - W).max())
+
+
 @pytest.mark.parametrize("model,dim", [(0, 2), (2, 2), (2, 3), (0, 3)])
 def test_grid_iterations_match_oracle(lib, model, dim):
     """The whole iteration to the stopping rule on small meshes (FP64)."""
