@@ -14,13 +14,16 @@
 // iteration all read the previous iterate, so their hulls are independent; only
 // the choice among them is ordered (a later direction replaces a node's value
 // only when lower by more than a rounding margin).  An iteration therefore runs,
-// per group of up to 16 directions, a hull launch -- one thread per line of every
-// direction of the group; the line starts (nodes whose predecessor lies outside
-// the box) form at most d*d disjoint boxes and are decoded from the thread index;
-// the thread stages its line in its own LDS column, builds the lower hull with a
-// monotone chain and writes every node's candidate value (and, when stresses or
-// moduli are carried, its laminate's offsets) -- then a pick launch, one thread
-// per node, that takes the group's candidates in direction order.  The last
+// per group of up to 16 directions with lines of more than three nodes, a hull
+// launch -- one thread per line of every such direction; the line starts (nodes
+// whose predecessor lies outside the box) form at most d*d disjoint boxes and are
+// decoded from the thread index; the thread stages its line in its own LDS
+// column, builds the lower hull with a monotone chain and writes every node's
+// candidate value (and, when stresses or moduli are carried, its laminate's
+// offsets) -- then a pick launch, one thread per node, that takes the candidates
+// in direction order.  Directions whose lines hold at most three nodes (166 of
+// the 169 of the paper's 3D mesh) need no hull launch: the pick forms their
+// candidate, the midpoint of a node's two neighbours, in place.  The last
 // pick of an iteration also takes the maximal decrease and writes the carried
 // stresses and moduli, so nothing is copied between iterations.
 #include <hip/hip_runtime.h>
@@ -114,9 +117,9 @@ inline int len_class(int len) {
 }
 
 struct Group {
-  int d0;                      // first direction of the group
   int n;                       // directions of this launch ...
-  int slot[kGroupMax];         // ... their slots in the group (direction d0 + slot)
+  int dir[kGroupMax];          // ... their indices
+  int slot[kGroupMax];         // ... their candidate slots in the group
   int block_end[kGroupMax];    // prefix sums of their blocks
 };
 
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(kLineThreads) void k_grid_hulls(GridArgs g, const S
 #pragma unroll
   for (int k = 0; k < kGroupMax; ++k) i += (k < grp.n && blk >= grp.block_end[k]) ? 1 : 0;
   const int j = grp.slot[i];
-  const Step& s = steps[grp.d0 + j];
+  const Step& s = steps[grp.dir[i]];
   const int64_t t0 = int64_t(blk - (i ? grp.block_end[i - 1] : 0)) * kLineThreads * R + tid;
   T* const cd = cand + int64_t(j) * g.size;
   uint32_t* const od = offs ? offs + int64_t(j) * g.size : nullptr;
@@ -254,19 +257,62 @@ __global__ __launch_bounds__(kLineThreads) void k_grid_hulls(GridArgs g, const S
   }
 }
 
-// The group's candidates in direction order, per node: a candidate replaces the
+// What the pick launch needs of a direction: the node index step; the slot of
+// its candidates, or -1 where the pick forms them itself (lines of at most three
+// nodes, steps of -1, 0, 1: only a node with both neighbours inside the box is
+// the middle of such a line); the bit mask of the components it steps.
+struct PickDir {
+  int32_t ds;
+  uint32_t need;
+  int32_t slot;
+  int32_t dir;
+};
+
+// Bit c set: node p has both neighbours in component c.
+template <int DD>
+__device__ __forceinline__ uint32_t interior_mask(const GridArgs& g, uint32_t p) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int c = DD - 1; c >= 0; --c) {
+    // p / n through FP64: (p + 1/2) / n is at least 1 / 1024 from an integer, and
+    // p < 2^31 leaves the product's rounding far below that
+    const uint32_t n = uint32_t(g.n[c]), q = uint32_t((double(p) + 0.5) * g.inv_n[c]), i = p - q * n;
+    m |= (i >= 1 && i + 1 < n) ? 1u << c : 0u;
+    p = q;
+  }
+  return m;
+}
+
+// The candidates of ne directions, in order, per node: a candidate replaces the
 // running value only when lower by more than 4 units of rounding relative to
 // max(|W|, 1e-3), so directions that tie to rounding leave the node to the first.
 // kFirst: the running value starts from Win (else Wout, and with sel the running
 // laminate) and every node is written.  Sparse (mask): only the marked slots of
-// the nodes with a mark are read, and the mask goes back to 0.
+// a node are read, and the mask goes back to 0.
 // The maximal decrease Win - W over nodes with finite Win goes to *dec (atomic
 // maximum of the non-negative doubles' bit patterns; W only decreases over the
 // groups, so the maximum over the nodes the groups lower is the iteration's).
 // kLast: the node stresses / moduli of the laminate that lowered a node, with the
 // weights of its value (eq. 5.2, first case), or the node's own, go to Pout / Aout.
+//
+// kNb: some directions have slot -1; the node reads its two neighbours for those.
+// Which of them concern a node depends only on its interior mask, so k_grid_lists
+// writes for each of the 2^(d*d) masks the directions to look at, in order (once
+// per call), and each lane works off its own mask's list, four directions at a
+// time so that eight loads are in flight: on the 5.8M-node 3D mesh 18 of the 169
+// directions per node on average, 30 per wave.  What bounds it is the issue of
+// those steps (FP64 compares and 64-bit addresses, about 45 instructions each) and
+// the latency of the neighbour reads.  On that mesh an iteration takes 0.45 ms
+// (pick 0.35, the three long directions' hulls 0.10) against 2.2 ms when every
+// direction had a hull launch and a candidate array; testing all 169 directions
+// per wave in scalar code instead of the lists took 1.33 ms.  The blocks take
+// contiguous node ranges, an eighth of the mesh per XCD, so that the neighbours
+// (up to 400,000 nodes away there) are found in that XCD's L2; 4096 blocks rather
+// than 2048 keep the 2D meshes at one strip of 256 nodes a block (pick 32 against
+// 42 us, 3D 0.35 against 0.45 ms).
 enum : int { kFirst = 1, kLast = 2 };
-constexpr unsigned kPickBlocks = 2048;  // grid-stride pick launches: 8 blocks per CU
+constexpr unsigned kPickBlocks = 4096;  // 16 blocks per CU, each a contiguous range of nodes
+constexpr int kPickBatch = 4;
 
 template <typename T>
 struct Carry {
@@ -278,8 +324,40 @@ struct Carry {
   uint32_t* soff;          // ... and its offsets, kept between groups
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, const Step* __restrict__ steps, int d0, int nd,
+// An entry of a mask's list: the node index step (0 where a slot holds the
+// candidate), and direction << 5 | slot + 1.
+__device__ __forceinline__ long long list_entry(const PickDir& d) {
+  const uint32_t ds = d.slot < 0 ? uint32_t(d.ds) : 0u;
+  return (long long)((unsigned long long)ds | (unsigned long long)uint32_t(d.dir << 5 | (d.slot + 1)) << 32);
+}
+
+// lists[M * pitch ..]: the entries of dirs that a node with interior mask M looks
+// at, in order, filled up to a multiple of kPickBatch with steps of 0 (the node is
+// its own neighbour, which lowers nothing); counts[M] their number.  One wave per mask.
+__global__ __launch_bounds__(64) void k_grid_lists(const PickDir* __restrict__ dirs, int ne, int pitch,
+                                                   long long* __restrict__ lists, int* __restrict__ counts) {
+  const uint32_t M = blockIdx.x;
+  const int lane = threadIdx.x;
+  long long* const list = lists + int64_t(M) * pitch;
+  int at = 0;
+  for (int e0 = 0; e0 < ne; e0 += 64) {
+    const int e = e0 + lane;
+    const PickDir d = dirs[e < ne ? e : 0];
+    const bool v = e < ne && (d.slot >= 0 || (d.need & ~M) == 0u);
+    const unsigned long long b = __ballot(v);
+    if (v) list[at + __popcll(b & ((1ull << lane) - 1ull))] = list_entry(d);
+    at += __popcll(b);
+  }
+  const int full = (at + kPickBatch - 1) / kPickBatch * kPickBatch;
+  if (at + lane < full) list[at + lane] = 0;
+  if (lane == 0) counts[M] = full;
+}
+
+template <typename T, int DD, bool kNb>
+__global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const Step* __restrict__ steps,
+                                                   const PickDir* __restrict__ dirs, int ne,
+                                                   int pitch, const longlong2* __restrict__ lists,
+                                                   const int* __restrict__ counts,
                                                    const T* __restrict__ Win, T* __restrict__ Wout,
                                                    const T* __restrict__ cand, const uint32_t* __restrict__ offs,
                                                    uint32_t* __restrict__ mask, Carry<T> cy, int flags,
@@ -287,58 +365,99 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, const Step* __res
   const int64_t n = g.size;
   const bool first = flags & kFirst;
   const bool carry = cy.Pout || cy.Aout;
+  // gridDim.x is a multiple of 8; blocks go to the 8 XCDs in turn
+  const int64_t blk = int64_t(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   double m = 0.0;
-  for (int64_t node = int64_t(blockIdx.x) * 256 + threadIdx.x; node < n; node += int64_t(gridDim.x) * 256) {
-    const uint32_t mk = mask ? mask[node] : (1u << nd) - 1u;
-    if (mk || first || (carry && (flags & kLast))) {
-      const T w0 = Win[node];
-      T cur = first || !mk ? w0 : Wout[node];
-      int32_t sl = -1;
-      uint32_t so = 0;
-      if (carry && !first) {
-        sl = cy.sel[node];
-        so = cy.soff[node];
-      }
-      bool changed = false;
-      if (mk) {
-        T v[kGroupMax];                            // all loads first, then the ordered choice
+  for (int strip = 0; strip < strips; ++strip) {
+    const int64_t p0 = (blk * strips + strip) * 256;
+    if (p0 >= n) break;                          // block-uniform
+    const int64_t node = p0 + threadIdx.x;
+    const bool live = node < n;
+    const T w0 = live ? Win[node] : inf_t<T>();
+    const uint32_t mk = !live ? 0u : mask ? mask[node] : ~0u;
+    T cur = first || !live ? w0 : Wout[node];
+    int32_t sl = -1;
+    uint32_t so = 0;
+    if (carry && !first && live) {
+      sl = cy.sel[node];
+      so = cy.soff[node];
+    }
+    bool changed = false;
+    int sslot = -1;                              // candidate slot of the laminate taken here
+    auto limit = [](T w) { return w - T(4) * eps_t<T>() * fmax(fabs(w), T(1e-3)); };
+    T lim = limit(cur);
+    auto take = [&](T c, int dir, int slot) {
+      cur = c;
+      lim = limit(c);
+      sl = dir;
+      sslot = slot;
+      changed = true;
+    };
+    if constexpr (kNb) {
+      // a node with no finite value of its own is the middle of nothing
+      const uint32_t in = live && w0 < inf_t<T>() ? interior_mask<DD>(g, uint32_t(node)) : 0u;
+      const int cnt = live ? counts[in] : 0;
+      const longlong2* const list = lists + int64_t(in) * (pitch / 2);
+      const T* const wn = Win + node;
+      const T* const cn = cand + node;
+      for (int k0 = 0; k0 < cnt; k0 += kPickBatch) {
+        const longlong2 e01 = list[k0 / 2], e23 = list[k0 / 2 + 1];
+        const long long e[kPickBatch] = {e01.x, e01.y, e23.x, e23.y};
+        T a[kPickBatch], b[kPickBatch];
 #pragma unroll
-        for (int j = 0; j < kGroupMax; ++j) v[j] = (mk >> j) & 1u ? cand[int64_t(j) * n + node] : inf_t<T>();
-        if (mask) mask[node] = 0u;
+        for (int j = 0; j < kPickBatch; ++j) {
+          const int64_t ds = int32_t(e[j]);
+          const uint32_t slot1 = uint32_t(e[j] >> 32) & 31u;      // slot + 1
+          a[j] = *(slot1 ? cn + uint64_t(slot1 - 1u) * uint32_t(n) : wn - ds);
+          b[j] = wn[ds];
+        }
 #pragma unroll
-        for (int j = 0; j < kGroupMax; ++j) {
-          if (v[j] < cur - T(4) * eps_t<T>() * fmax(fabs(cur), T(1e-3))) {
-            cur = v[j];
-            sl = d0 + j;
-            if (offs) so = offs[int64_t(j) * n + node];
-            changed = true;
-          }
+        for (int j = 0; j < kPickBatch; ++j) {
+          const uint32_t code = uint32_t(e[j] >> 32), slot1 = code & 31u;
+          // the monotone chain on three nodes: the middle one is popped exactly when
+          // it lies on or above the chord, and its candidate is the chord's midpoint
+          // (an absent neighbour, +inf or NaN, fails the comparisons)
+          const bool cut = w0 - a[j] >= b[j] - w0;
+          const bool ok = slot1 ? ((mk >> (slot1 - 1u)) & 1u) != 0u : cut;
+          const T c = slot1 ? a[j] : (a[j] + b[j]) / T(2);
+          if (ok && c < lim) take(c, int(code >> 5), int(slot1) - 1);
         }
       }
-      if (first || changed) Wout[node] = cur;
-      if (changed && w0 < inf_t<T>()) m = fmax(m, double(w0) - double(cur));
-      if (carry && !(flags & kLast) && (first || changed)) {
-        cy.sel[node] = sl;
-        cy.soff[node] = so;
+    } else {
+      T v[kGroupMax];                            // all loads first, then the ordered choice
+#pragma unroll
+      for (int j = 0; j < kGroupMax; ++j)
+        v[j] = j < ne && live && ((mk >> j) & 1u) ? cand[int64_t(j) * n + node] : inf_t<T>();
+#pragma unroll
+      for (int j = 0; j < kGroupMax; ++j)
+        if (j < ne && v[j] < lim) take(v[j], dirs[j].dir, j);
+    }
+    if (!live) continue;
+    if (changed) so = sslot < 0 ? 1u | (1u << 16) : offs ? offs[int64_t(sslot) * n + node] : 0u;
+    if (mask && mk) mask[node] = 0u;
+    if (first || changed) Wout[node] = cur;
+    if (changed && w0 < inf_t<T>()) m = fmax(m, double(w0) - double(cur));
+    if (carry && !(flags & kLast) && (first || changed)) {
+      cy.sel[node] = sl;
+      cy.soff[node] = so;
+    }
+    if (carry && (flags & kLast)) {
+      int64_t ia = node, ib = node;
+      int qa = 0, bq = 0;
+      if (sl >= 0) {
+        qa = int(so & 0xffffu);
+        bq = int(so >> 16);
+        ia = node - qa * steps[sl].ds;
+        ib = node + bq * steps[sl].ds;
       }
-      if (carry && (flags & kLast)) {
-        int64_t ia = node, ib = node;
-        int qa = 0, bq = 0;
-        if (sl >= 0) {
-          qa = int(so & 0xffffu);
-          bq = int(so >> 16);
-          ia = node - qa * steps[sl].ds;
-          ib = node + bq * steps[sl].ds;
-        }
-        if (cy.Pout)
-          for (int c = 0; c < g.dd; ++c)
-            cy.Pout[c * n + node] = sl < 0 ? cy.Pin[c * n + node]
-                                           : (T(bq) * cy.Pin[c * n + ia] + T(qa) * cy.Pin[c * n + ib]) / T(qa + bq);
-        if (cy.Aout)
-          for (int c = 0; c < g.dd * g.dd; ++c)
-            cy.Aout[c * n + node] = sl < 0 ? cy.Ain[c * n + node]
-                                           : (T(bq) * cy.Ain[c * n + ia] + T(qa) * cy.Ain[c * n + ib]) / T(qa + bq);
-      }
+      if (cy.Pout)
+        for (int c = 0; c < DD; ++c)
+          cy.Pout[c * n + node] = sl < 0 ? cy.Pin[c * n + node]
+                                         : (T(bq) * cy.Pin[c * n + ia] + T(qa) * cy.Pin[c * n + ib]) / T(qa + bq);
+      if (cy.Aout)
+        for (int c = 0; c < DD * DD; ++c)
+          cy.Aout[c * n + node] = sl < 0 ? cy.Ain[c * n + node]
+                                         : (T(bq) * cy.Ain[c * n + ia] + T(qa) * cy.Ain[c * n + ib]) / T(qa + bq);
     }
   }
   // one atomic per block (the launch has a bounded number of blocks)
@@ -418,6 +537,9 @@ struct GridWork {
   T* A2 = nullptr;
   unsigned long long* dec = nullptr;
   Step* steps = nullptr;
+  PickDir* dirs = nullptr;
+  long long* lists = nullptr;  // k_grid_lists, 2^(d*d) masks per group with neighbour directions
+  int* counts = nullptr;
   T* cand = nullptr;
   uint32_t* offs = nullptr;
   uint32_t* mask = nullptr;    // sparse mode only
@@ -428,27 +550,76 @@ struct GridWork {
 inline size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 
 
-// One iteration: for each group of directions, the hull launch then the pick launch.
+// The direction's candidates are formed by the pick launch: lines of at most three
+// nodes, at consecutive mesh nodes.
+inline bool by_neighbours(const GridArgs& g, const Step& s) {
+  for (int c = 0; c < g.dd; ++c)
+    if (s.s[c] < -1 || s.s[c] > 1) return false;
+  return s.len <= 3;
+}
+
+// The iteration's work list: the directions in order without those whose lines
+// hold fewer than three nodes (no node strictly inside a segment), cut into
+// groups with at most kGroupMax hull directions each.
+struct Segment {
+  int e0, n;               // entries of the pick launch
+  bool neighbours;         // some entry is formed from neighbours ...
+  int pitch;               // ... then the entries per interior mask in its lists
+  int64_t list0;           // ... and the lists' offset
+};
+
+inline void plan_groups(const GridArgs& g, const std::vector<Step>& steps, std::vector<PickDir>* dirs,
+                        std::vector<Segment>* segs) {
+  int slots = 0;
+  segs->push_back(Segment{});
+  for (size_t d = 0; d < steps.size(); ++d) {
+    const Step& s = steps[d];
+    if (s.len < 3) continue;
+    const bool nb = by_neighbours(g, s);
+    if (!nb && slots == kGroupMax) {
+      segs->push_back(Segment{int(dirs->size())});
+      slots = 0;
+    }
+    PickDir p{};
+    p.ds = int32_t(s.ds);
+    p.slot = nb ? -1 : slots++;
+    p.dir = int32_t(d);
+    for (int c = 0; c < g.dd; ++c) p.need |= s.s[c] != 0 ? 1u << c : 0u;
+    dirs->push_back(p);
+    segs->back().n += 1;
+    segs->back().neighbours |= nb;
+  }
+  int64_t at = 0;
+  for (Segment& sg : *segs) {
+    sg.pitch = (sg.n + kPickBatch - 1) / kPickBatch * kPickBatch;
+    sg.list0 = at;
+    if (sg.neighbours) at += int64_t(sg.pitch) << g.dd;
+  }
+}
+
+// One iteration: for each group of directions, the hull launches then the pick launch.
 template <typename T>
-hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const GridWork<T>& wk, const T* Win,
+hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const std::vector<PickDir>& dirs,
+                      const std::vector<Segment>& segs, const GridWork<T>& wk, const T* Win,
                       T* Wout, Carry<T> cy, unsigned long long* dec, hipStream_t st, KTimer* tm) {
-  const int n_dir = int(steps.size());
   const bool carry = cy.Pout || cy.Aout;
-  for (int d0 = 0; d0 < n_dir; d0 += kGroupMax) {
-    const int nd = std::min(kGroupMax, n_dir - d0);
+  for (size_t sg = 0; sg < segs.size(); ++sg) {
+    const Segment& seg = segs[sg];
     // one hull launch per length class of the group's lines, each with the LDS of
     // its own longest line (short lines would otherwise run at the occupancy of the
     // longest); the candidates keep their group slots, so the order is unchanged
     for (int part = 0; part < kLenClasses; ++part) {
       const int R = part == 0 ? kShortRun : 1;
       Group grp{};
-      grp.d0 = d0;
       int blocks = 0, len = 1;
-      for (int j = 0; j < nd; ++j) {
-        const Step& s = steps[d0 + j];
+      for (int j = 0; j < seg.n; ++j) {
+        const PickDir& p = dirs[size_t(seg.e0 + j)];
+        if (p.slot < 0) continue;
+        const Step& s = steps[size_t(p.dir)];
         if (len_class(s.len) != part) continue;
         blocks += int(blocks_of(s.count, kLineThreads * R));
-        grp.slot[grp.n] = j;
+        grp.dir[grp.n] = p.dir;
+        grp.slot[grp.n] = p.slot;
         grp.block_end[grp.n] = blocks;
         ++grp.n;
         len = std::max(len, s.len);
@@ -470,14 +641,19 @@ hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const G
                            wk.cand, offs, wk.mask, len);
       if (tm) tm->end(st);
     }
-    const int flags = (d0 == 0 ? kFirst : 0) | (d0 + nd == n_dir ? kLast : 0);
+    const int flags = (sg == 0 ? kFirst : 0) | (sg + 1 == segs.size() ? kLast : 0);
     Carry<T> c = cy;
     c.sel = carry ? wk.sel : nullptr;
     c.soff = carry ? wk.soff : nullptr;
     if (tm) tm->begin("grid_pick", st);
-    hipLaunchKernelGGL((k_grid_pick<T>), dim3(std::min<unsigned>(blocks_of(g.size, 256), kPickBlocks)), dim3(256), 0,
-                       st, g, wk.steps, d0, nd,
-                       Win, Wout, wk.cand, carry ? wk.offs : nullptr, wk.mask, c, flags, dec);
+    const unsigned pick_blocks = std::min<unsigned>((blocks_of(g.size, 256) + 7u) & ~7u, kPickBlocks);
+    const unsigned strips = (blocks_of(g.size, 256) + pick_blocks - 1) / pick_blocks;   // of 256 nodes, per block
+    const auto pick = g.dd == 4 ? (seg.neighbours ? k_grid_pick<T, 4, true> : k_grid_pick<T, 4, false>)
+                                : (seg.neighbours ? k_grid_pick<T, 9, true> : k_grid_pick<T, 9, false>);
+    hipLaunchKernelGGL(pick, dim3(pick_blocks), dim3(256), 0, st, g, int(strips), wk.steps, wk.dirs + seg.e0, seg.n,
+                       seg.pitch, reinterpret_cast<const longlong2*>(wk.lists + seg.list0),
+                       wk.counts + (int64_t(sg) << g.dd), Win, Wout, wk.cand, carry ? wk.offs : nullptr, wk.mask, c,
+                       flags, dec);
     if (tm) tm->end(st);
   }
   return hipGetLastError();
@@ -489,8 +665,15 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
                           T* A, int k_max, double tol, int32_t* iterations, double* decrease, hipStream_t st) {
   const size_t n = size_t(g.size);
   const bool carry = P || A;
-  const int G = std::min<int>(kGroupMax, int(steps.size()));
-  const size_t sizes[10] = {round256(sizeof(T) * n),
+  std::vector<PickDir> dirs;
+  std::vector<Segment> segs;
+  plan_groups(g, steps, &dirs, &segs);
+  int G = 0;                                  // candidate slots
+  for (const PickDir& p : dirs) G = std::max(G, p.slot + 1);
+  size_t list_len = 0;
+  for (const Segment& sg : segs)
+    if (sg.neighbours) list_len = size_t(sg.list0) + (size_t(sg.pitch) << g.dd);
+  const size_t sizes[13] = {round256(sizeof(T) * n),
                            P ? round256(sizeof(T) * n * size_t(g.dd)) : 0,
                            A ? round256(sizeof(T) * n * size_t(g.dd * g.dd)) : 0,
                            round256(sizeof(unsigned long long) * size_t(k_max)),
@@ -499,7 +682,10 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
                            carry ? round256(sizeof(uint32_t) * n * size_t(G)) : 0,
                            carry ? round256(sizeof(int32_t) * n) : 0,
                            carry ? round256(sizeof(uint32_t) * n) : 0,
-                           sparse ? round256(sizeof(uint32_t) * n) : 0};
+                           sparse ? round256(sizeof(uint32_t) * n) : 0,
+                           round256(sizeof(PickDir) * std::max<size_t>(dirs.size(), 1)),
+                           list_len ? round256(sizeof(long long) * list_len) : 0,
+                           list_len ? round256(sizeof(int) * (segs.size() << g.dd)) : 0};
   size_t total = 0;
   for (size_t b : sizes) total += b;
   void* base = nullptr;
@@ -522,12 +708,21 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
   wk.sel = static_cast<int32_t*>(take(7));
   wk.soff = static_cast<uint32_t*>(take(8));
   wk.mask = static_cast<uint32_t*>(take(9));
+  wk.dirs = static_cast<PickDir*>(take(10));
+  wk.lists = static_cast<long long*>(take(11));
+  wk.counts = static_cast<int*>(take(12));
   hipError_t e = hipMemcpyAsync(wk.steps, steps.data(), sizeof(Step) * steps.size(), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess && !dirs.empty())
+    e = hipMemcpyAsync(wk.dirs, dirs.data(), sizeof(PickDir) * dirs.size(), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return r1h::fail(h, e, "grid steps");
   if (sparse)  // the invariant the sparse launches keep: no marks between groups
     hipLaunchKernelGGL((k_grid_fill<uint32_t>), dim3(blocks_of(int64_t(n), 256)), dim3(256), 0, st, int64_t(n),
                        wk.mask, 0u);
   hipLaunchKernelGGL(k_grid_zero, dim3(blocks_of(k_max, 256)), dim3(256), 0, st, wk.dec, k_max);
+  for (size_t k = 0; k < segs.size(); ++k)
+    if (segs[k].neighbours)
+      hipLaunchKernelGGL(k_grid_lists, dim3(1u << g.dd), dim3(64), 0, st, wk.dirs + segs[k].e0, segs[k].n,
+                         segs[k].pitch, wk.lists + segs[k].list0, wk.counts + (int64_t(k) << g.dd));
   KTimer* tm = h->timer.on ? &h->timer : nullptr;
   T* cur = W;
   T* nxt = wk.W2;
@@ -538,7 +733,7 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
   int k = 0;
   while (k < k_max) {
     Carry<T> cy{pcur, pnxt, acur, anxt, nullptr, nullptr};
-    e = grid_sweep<T>(g, steps, wk, cur, nxt, cy, wk.dec + k, st, tm);
+    e = grid_sweep<T>(g, steps, dirs, segs, wk, cur, nxt, cy, wk.dec + k, st, tm);
     unsigned long long bits = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&bits, wk.dec + k, sizeof(bits), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -659,18 +854,23 @@ r1_status r1_grid_laminate(r1_handle h, const r1_grid* grid, int32_t n_dir, cons
     if (zero) return R1_EINVAL;
   }
   // sparse when the lines of at least 3 nodes -- the only ones that can lower a
-  // node -- cover under half of the direction-node pairs (the 9-D meshes: under a
-  // third; the 4-D ones: nearly all)
+  // node -- of the directions with hull launches cover under half of those
+  // direction-node pairs (4-D meshes and the long directions of the paper's 9-D
+  // mesh: nearly all)
   double covered = 0.0;
+  int hulls = 0;
   for (int m = 0; m < n_dir; ++m) {
     Step t = st_list[m];
+    step_slabs(g, &t, 1);
+    if (t.len < 3 || by_neighbours(g, t)) continue;
+    ++hulls;
     for (int len = 3; len <= kGridMaxLen; ++len) {
       step_slabs(g, &t, len);
       if (t.count == 0) break;
       covered += double(t.count) * (len == 3 ? 3.0 : 1.0);
     }
   }
-  const bool sparse = covered < 0.5 * double(n_dir) * double(g.size);
+  const bool sparse = covered < 0.5 * double(hulls) * double(g.size);
   for (int m = 0; m < n_dir; ++m) step_slabs(g, &st_list[m], sparse ? 3 : 1);
   hipError_t e = hipSetDevice(h->device);
   if (e != hipSuccess) return r1h::fail(h, e, "hipSetDevice");

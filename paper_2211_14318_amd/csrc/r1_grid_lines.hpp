@@ -31,6 +31,7 @@ struct GridArgs {
   int n[9];                // nodes per component (1 beyond dd)
   int64_t stride[9];       // node index step of each component (component 0 slowest)
   double lo[9];            // first node value per component
+  double inv_n[9];         // 1 / n
   double delta;            // mesh width
   int64_t size;            // nodes
 };
@@ -66,6 +67,7 @@ inline r1_status grid_args(const r1_grid* grid, GridArgs* g) {
     g->n[c] = 1;
     g->lo[c] = 0.0;
   }
+  for (int c = 0; c < 9; ++c) g->inv_n[c] = 1.0 / double(g->n[c]);
   int64_t st = 1;
   for (int c = g->dd - 1; c >= 0; --c) {
     g->stride[c] = st;

@@ -175,6 +175,40 @@ def test_grid_every_hull_path_on_random_values(lib, kind, n):
                                                                                        len(differ)))
 
 
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,n", [(2, (3, 4, 3, 21)), (3, (4, 4, 2, 3, 4, 4, 2, 3, 4))])
+def test_grid_neighbour_directions_on_random_values(lib, kind, dim, n):
+    """Directions with lines of at most three nodes (candidates formed from a node's two
+    neighbours) among directions with longer ones; the 3D mesh needs more than one group of
+    hull directions, with neighbour directions in each.  One iteration from random values
+    with +inf holes, random stresses carried, against the oracle's sweep."""
+    r1, h, torch = lib
+    dt = torch.float64 if kind == "f64" else torch.float32
+    lo = [0.5 if i % (dim + 1) == 0 else -0.2 for i in range(dim * dim)]
+    g, og = both_grids(r1, dim, n, lo, 0.05)
+    N, dd = O.grid_size(og), dim * dim
+    rng = np.random.default_rng(72 + dim)
+    W0 = rng.normal(size=N)
+    W0[rng.random(N) < 0.05] = np.inf
+    P0 = rng.normal(size=(dd, N))
+    W = torch.tensor(W0, dtype=dt, device="cuda")
+    P = torch.tensor(P0, dtype=dt, device="cuda")
+    hist = h.grid_laminate(g, r1.grid_r11(dim), W, k_max=1, tol=0.0, P=P)
+    torch.cuda.synchronize()
+    Wi = torch.tensor(W0, dtype=dt).double().numpy()
+    Pi = torch.tensor(P0, dtype=dt).double().numpy()
+    ref, md, Pref = O.grid_sweep(og, O.grid_r11(dim), Wi, Pi)
+    Wg, Pg = W.double().cpu().numpy(), P.double().cpu().numpy()
+    fin = np.isfinite(ref)
+    tol = 1e-15 if kind == "f64" else 2e-6
+    assert np.array_equal(np.isfinite(Wg), fin)
+    assert np.max(np.abs(Wg[fin] - ref[fin])) <= tol and abs(hist[0] - md) <= tol
+    ctol = 1e-14 if kind == "f64" else 2e-6
+    differ = np.nonzero(fin & np.any(np.abs(Pg - Pref) > ctol * np.maximum(np.abs(Pref).max(axis=0), 1.0), axis=0))[0]
+    check_laminate_validity(n, O.grid_r11(dim), Wi, Pi, Wg, Pg, differ, 2.0 ** -52 if kind == "f64" else 2.0 ** -23, ctol)
+    assert len(differ) <= N // 100
+
+
 def test_grid_decrease_is_the_maximum_over_all_nodes(lib):
     """The maximal decrease of an iteration on a mesh of more nodes than the pick launch has
     threads (each thread visits several nodes): the largest of W^k - W^{k+1}, exactly."""
