@@ -485,12 +485,19 @@ __global__ __launch_bounds__(256) void k_grid_zero(unsigned long long* dec, int 
 
 // Multilinear interpolation of the node values at n points F (SoA, d*d x n):
 // corners of zero weight do not take part; NaN outside the box (beyond a
-// rounding margin of 1e-9 mesh widths).
-template <typename T, int D>
+// rounding margin of 1e-9 mesh widths).  LP lanes share a point: lane sub of them
+// takes the corners whose leading log2(LP) bits (one per component, the slowest
+// first) are sub, so its own corners are the nearest in memory, and the lanes'
+// sums meet in a butterfly.
+template <typename T, int D, int LP>
 __global__ __launch_bounds__(256) void k_grid_interp(GridArgs g, const T* W, int64_t n, const T* F, T* out) {
-  const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (p >= n) return;
+  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t p = t / LP;
+  const int sub = int(t % LP);
+  if (p >= n) return;                            // whole groups of LP lanes
   constexpr int DD = D * D;
+  constexpr int kLead = LP == 64 ? 6 : 0;
+  static_assert((1 << kLead) == LP && kLead <= DD, "lanes per point");
   int base[DD];
   double frac[DD];
   bool inside = true;
@@ -507,15 +514,25 @@ __global__ __launch_bounds__(256) void k_grid_interp(GridArgs g, const T* W, int
     frac[c] = g.n[c] > 1 ? u - i : 0.0;
   }
   if (!inside) {
-    out[p] = T(__builtin_nan(""));
+    if (sub == 0) out[p] = T(__builtin_nan(""));
     return;
   }
-  double sum = 0.0;
-  for (int corner = 0; corner < (1 << DD); ++corner) {
-    double wgt = 1.0;
-    int64_t idx = 0;
+  double lead = 1.0;                             // weight and node index of the lane's leading bits
+  int64_t at = 0;
 #pragma unroll
-    for (int c = 0; c < DD; ++c) {
+  for (int c = 0; c < kLead; ++c) {
+    const int up = (sub >> (kLead - 1 - c)) & 1;
+    if (up && g.n[c] == 1) lead = 0.0;
+    lead *= up ? frac[c] : 1.0 - frac[c];
+    at += int64_t(base[c] + up) * g.stride[c];
+  }
+  double sum = 0.0;
+#pragma unroll 8
+  for (int corner = 0; corner < (1 << (DD - kLead)); ++corner) {
+    double wgt = lead;
+    int64_t idx = at;
+#pragma unroll
+    for (int c = kLead; c < DD; ++c) {
       const int up = (corner >> (DD - 1 - c)) & 1;
       if (up && g.n[c] == 1) wgt = 0.0;
       wgt *= up ? frac[c] : 1.0 - frac[c];
@@ -523,7 +540,9 @@ __global__ __launch_bounds__(256) void k_grid_interp(GridArgs g, const T* W, int
     }
     if (wgt != 0.0) sum += wgt * double(W[idx]);
   }
-  out[p] = T(sum);
+#pragma unroll
+  for (int o = LP / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (sub == 0) out[p] = T(sum);
 }
 
 inline unsigned blocks_of(int64_t n, int b) { return unsigned((n + b - 1) / b); }
@@ -771,6 +790,26 @@ void launch_energy(int dim, dim3 grd, hipStream_t st, const GridArgs& g, const r
     hipLaunchKernelGGL((k_grid_energy<T, 3>), grd, dim3(256), 0, st, g, m, beta_n, w, p, a);
 }
 
+// Lanes per point: in 3D a point reads 512 corners, and one lane each for a few
+// thousand points leaves the chip idle behind long chains of loads; a whole wave
+// per point repeats the point's set-up on every lane and fills the chip earlier.
+// FP64 on the 5.8M-node mesh, a lane / a wave per point: 2003 points 357 / 14 us,
+// 32767 points 353 / 166 us, equal near 65,000 points (0.34 ms), beyond which the
+// wave per point grows with the points and the lane per point does not yet.  In 2D
+// the 16 corners are one round of loads.
+template <typename T>
+void launch_interp(int dim, const GridArgs& g, const void* W, int64_t n, const void* F, void* out, hipStream_t st) {
+  const T* w = static_cast<const T*>(W);
+  const T* f = static_cast<const T*>(F);
+  T* o = static_cast<T*>(out);
+  if (dim == 2)
+    hipLaunchKernelGGL((k_grid_interp<T, 2, 1>), dim3(blocks_of(n, 256)), dim3(256), 0, st, g, w, n, f, o);
+  else if (n < 65536)
+    hipLaunchKernelGGL((k_grid_interp<T, 3, 64>), dim3(blocks_of(n * 64, 256)), dim3(256), 0, st, g, w, n, f, o);
+  else
+    hipLaunchKernelGGL((k_grid_interp<T, 3, 1>), dim3(blocks_of(n, 256)), dim3(256), 0, st, g, w, n, f, o);
+}
+
 }  // namespace
 
 extern "C" {
@@ -894,22 +933,10 @@ r1_status r1_grid_interpolate(r1_handle h, const r1_grid* grid, r1_dtype dtype, 
   hipError_t e = hipSetDevice(h->device);
   if (e != hipSuccess) return r1h::fail(h, e, "hipSetDevice");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const dim3 grd(blocks_of(n, 256));
-  if (dtype == R1_F32) {
-    if (grid->dim == 2)
-      hipLaunchKernelGGL((k_grid_interp<float, 2>), grd, dim3(256), 0, st, g, static_cast<const float*>(W), n,
-                         static_cast<const float*>(F), static_cast<float*>(out));
-    else
-      hipLaunchKernelGGL((k_grid_interp<float, 3>), grd, dim3(256), 0, st, g, static_cast<const float*>(W), n,
-                         static_cast<const float*>(F), static_cast<float*>(out));
-  } else {
-    if (grid->dim == 2)
-      hipLaunchKernelGGL((k_grid_interp<double, 2>), grd, dim3(256), 0, st, g, static_cast<const double*>(W), n,
-                         static_cast<const double*>(F), static_cast<double*>(out));
-    else
-      hipLaunchKernelGGL((k_grid_interp<double, 3>), grd, dim3(256), 0, st, g, static_cast<const double*>(W), n,
-                         static_cast<const double*>(F), static_cast<double*>(out));
-  }
+  if (dtype == R1_F32)
+    launch_interp<float>(grid->dim, g, W, n, F, out, st);
+  else
+    launch_interp<double>(grid->dim, g, W, n, F, out, st);
   e = hipGetLastError();
   return e == hipSuccess ? R1_OK : r1h::fail(h, e, "kernel launch");
 }

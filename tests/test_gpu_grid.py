@@ -314,6 +314,31 @@ def test_grid_interpolation_matches_oracle(lib, kind, dim):
     assert np.max(np.abs(got[ok] - ref[ok])) <= tol
 
 
+@pytest.mark.parametrize("n_pts", [1, 3, 65535, 65536])
+def test_grid_interpolation_lanes_per_point(lib, n_pts):
+    """3D interpolation on both sides of the switch between a wave and a lane per point:
+    an affine function of F is reproduced, a +inf node with weight is passed on, one without
+    weight (a component with a single node, a point on a node) is not."""
+    r1, h, torch = lib
+    n, lo, d = (3, 2, 1, 2, 4, 2, 2, 2, 3), [0.8, -0.1, 0.3, -0.1, 0.7, -0.1, -0.1, -0.1, 0.8], 0.25
+    g = r1.grid(3, n, lo, d)
+    rng = np.random.default_rng(83)
+    coef = rng.normal(size=9)
+    ax = np.meshgrid(*[lo[c] + d * np.arange(n[c]) for c in range(9)], indexing="ij")
+    W = sum(coef[c] * ax[c] for c in range(9)).ravel()
+    W[-1] = np.inf                                    # the last corner of the box
+    u = rng.random((9, n_pts)) * (np.array(n)[:, None] - 1)
+    u[:, 0] = 0.0                                     # on the first node
+    F = np.array(lo)[:, None] + d * u
+    out = h.grid_interpolate(g, torch.tensor(W, device="cuda"), torch.tensor(F, device="cuda").contiguous())
+    got = out.cpu().numpy()
+    near = np.all((np.array(n)[:, None] == 1) | (u > np.array(n)[:, None] - 2), axis=0)   # the last corner has weight
+    # 512 products of ten factors and a sum of 512 terms of at most sum |coef F| in FP64
+    bound = 2.0 ** -53 * (10 + 512) * np.sum(np.abs(coef)[:, None] * np.abs(np.array(lo)[:, None] + d * (np.array(n)[:, None] - 1) + d), axis=0).max()
+    assert np.array_equal(np.isinf(got), near)
+    assert np.max(np.abs(got[~near] - coef @ F[:, ~near])) <= bound
+
+
 def test_grid_invalid_arguments(lib):
     r1, h, torch = lib
     g = r1.grid(2, (3, 3, 3, 3), (0, 0, 0, 0), 0.5)
