@@ -348,10 +348,10 @@ r1_status r1_grid_energy(r1_handle handle, const r1_material* material, const r1
  * second case off the mesh.  Uses handle workspace of up to 17 node arrays of
  * dtype (the other iterate and the candidates of up to 16 directions); when P or
  * A is given, also one array like each, one uint32 per node and candidate slot
- * and two int32 per node for the laminates; one uint32 mask per node on
- * meshes where the lines of at least 3 nodes are a minority; and 8 bytes per
- * direction and each of 2^(dim*dim) node positions where some directions' lines
- * hold at most 3 nodes (no candidates are kept for those).  Synchronizes
+ * and two int32 per node for the laminates; up to 17 bytes per node for marks; and 8
+ * bytes per direction and each of 2^(dim*dim) node positions where some
+ * directions' lines hold at most 3 nodes (no candidates are kept for those).
+ * Synchronizes
  * `stream` once per iteration. */
 r1_status r1_grid_laminate(r1_handle handle, const r1_grid* grid, int32_t n_dir, const int32_t* steps,
                            r1_dtype dtype, void* W, void* P, void* A, int32_t k_max, double tol,

@@ -43,7 +43,7 @@ namespace {
 
 using namespace r1g;
 
-constexpr int kLineThreads = 64;        // threads per block of the line kernel
+constexpr int kLineThreads = 64;        // lines per wave of the hull kernels
 constexpr int kStageBytes = 56 * 1024;  // LDS of a block that stages its lines
 
 __device__ __forceinline__ void node_multi(const GridArgs& g, int64_t p, int* I) {
@@ -90,85 +90,229 @@ __global__ __launch_bounds__(256) void k_grid_energy(GridArgs g, r1d::Material m
 }
 
 // Hulls of some directions of a group of up to kGroupMax directions of one
-// iteration.  A block takes R * 64 consecutive line starts of one direction, its
-// lanes R of them 64 apart (lanes on consecutive starts, so accesses coalesce;
-// the first decoded, the next ones stepped to by a mixed-radix add).  The blocks
-// of the launch's i-th direction, group slot slot[i], are block_end[i-1] ..
-// block_end[i]-1, so a block's direction (and its Step, read through scalar
-// loads) is uniform.
+// iteration, one thread per line, 64 consecutive line starts of one direction per
+// wave (so accesses coalesce).  The blocks of the launch's i-th direction, group
+// slot slot[i], are block_end[i-1] .. block_end[i]-1, so a block's direction (and
+// its Step, read through scalar loads) is uniform.  Only the lines of at least 3
+// nodes are covered (shorter ones hold no node strictly inside a segment).
 // A node's candidate is the hull value ((b - q) w_a + (q - a) w_b) / (b - a)
-// where it lies strictly inside a hull segment [a, b] and its own value is
-// finite, +inf otherwise; with offs, also the offsets (q - a) | (b - q) << 16 of
-// its laminate.  Dense (mask null): the launch covers every line and writes
-// every slot (the lines of a direction partition the mesh, so each once).
-// Sparse: it covers only the lines of at least 3 nodes (shorter ones hold no
-// node strictly inside a segment), writes the finite candidates only and marks
-// them in the node's mask (bit = group slot); unmarked slots are never read.
-// Non-finite values are absent from a hull.  STAGED: the line's values sit in
-// the thread's LDS column (entry q at [q * kLineThreads]); otherwise they are
-// read in place.
+// where it lies strictly inside a hull segment [a, b] and its own value is finite;
+// with offs, also the offsets (q - a) | (b - q) << 16 of its laminate.  Non-finite
+// values are absent from a hull.  Only candidates that the pick could take (lower
+// than the node's own value by more than its margin: the running value it is
+// compared with is never above the node's own) are written, and marked in the
+// node's mark byte of the group slot; unmarked slots are never read.  A node has 4
+// mark bytes when no group has more than 4 hull directions, else 16 (each written
+// by one thread, so plain stores do: an atomic bit mask took the 5.8M-node mesh's
+// hulls from 0.10 to 0.13 ms).
 constexpr int kGroupMax = 16;
-constexpr int kShortLine = 8;  // lines of at most this many nodes go to their own hull launch
-constexpr int kShortRun = 8;   // line starts per thread there
-constexpr int kLenClasses = 6; // hull launches per group: lines of <= 8, 16, 32, 64, 128 nodes, longer
-
-inline int len_class(int len) {
-  return len <= kShortLine ? 0 : len <= 16 ? 1 : len <= 32 ? 2 : len <= 64 ? 3 : len <= 128 ? 4 : 5;
-}
+constexpr int kBitLine = 64;   // lines of at most this many nodes keep their hull as a bit mask
 
 struct Group {
   int n;                       // directions of this launch ...
   int dir[kGroupMax];          // ... their indices
   int slot[kGroupMax];         // ... their candidate slots in the group
+  int waves[kGroupMax];        // ... the waves of a block that take lines of it (their LDS is a block's share)
   int block_end[kGroupMax];    // prefix sums of their blocks
 };
 
-// One line of L nodes from node p, index step ds: hull, then the candidates.
-template <typename T, bool STAGED, int CHUNK>
-__device__ __forceinline__ void hull_line(const T* __restrict__ Win, T* __restrict__ cd, uint32_t* __restrict__ od,
-                                          uint32_t* __restrict__ mask, uint32_t bit, int64_t p, int64_t ds, int L,
-                                          T* vin, uint16_t* st) {
-  if (L == 3) {
-    // three nodes (most lines of the 9-D meshes): the chain pops the middle one
-    // exactly when it lies on or above the chord, and its candidate is the chord's
-    // midpoint -- the general path's arithmetic, without its loops
-    const T w0 = Win[p], w1 = Win[p + ds], w2 = Win[p + 2 * ds];
-    const bool fin = w0 < inf_t<T>() && w1 < inf_t<T>() && w2 < inf_t<T>();
-    const bool cand1 = fin && (w1 - w0) * T(1) >= (w2 - w1) * T(1);
-    const T val = cand1 ? (T(1) * w0 + T(1) * w2) / T(2) : inf_t<T>();
-    if (!mask) {
-      cd[p] = inf_t<T>();
-      cd[p + 2 * ds] = inf_t<T>();
-      if (od) od[p] = od[p + 2 * ds] = 0u;
+// What a candidate has to stay below to lower a node of value w (see k_grid_pick).
+template <typename T>
+__device__ __forceinline__ T pick_limit(T w) { return w - T(4) * eps_t<T>() * fmax(fabs(w), T(1e-3)); }
+
+// The direction of a block, its wave's share of the block's LDS, and this thread's
+// line start of the direction.
+struct LineRef {
+  int slot, dir, waves;
+  int64_t t;
+};
+__device__ __forceinline__ LineRef line_of_block(const Group& grp, int blk, int tid) {
+  int i = 0;
+#pragma unroll
+  for (int k = 0; k < kGroupMax; ++k) i += (k < grp.n && blk >= grp.block_end[k]) ? 1 : 0;
+  return LineRef{grp.slot[i], grp.dir[i], grp.waves[i],
+                 int64_t(blk - (i ? grp.block_end[i - 1] : 0)) * grp.waves[i] * kLineThreads + tid};
+}
+
+// Lines of at most 64 nodes.  A block of 4 waves shares lds_bytes of LDS: 4, 2 or 1
+// of its waves take lines, as many as their columns fit (entry q of a thread's line
+// at [q * kLineThreads] of its wave's share), so that one launch holds the short
+// lines at full occupancy and the few long ones beside them.
+//   ch (nullable): nodes that the previous iteration changed.  A line without one
+// has the candidates it had then, and none of them lowers its node: the node was
+// offered it and kept a value that it does not lie below by the margin, or has
+// taken a lower one since.  A wave without such a line ends before it reads a value.
+//   A line whose consecutive differences grow strictly pops nothing from the
+// monotone chain and has no candidate; a wave of such lines ends when it has read
+// them.  Otherwise each line runs the chain through its LDS column from its first
+// pop on (from its start where a value is absent): the top vertex is popped while
+// the slope into it is at least the slope from it to the new point (collinear
+// points are not kept), in one flat loop of pops and pushes, the vertices a bit
+// mask, the next value and the third vertex read ahead.
+//   What bounds it is instruction issue in the reading (about 10 per node) and the
+// latency of the chains that are left.  672,400-node 2D mesh, 14 directions of
+// 20-node and 2 of 41-node lines, FP64: 64 us an iteration, against 135 us with a
+// launch per length class, index stacks in LDS, every candidate written and every
+// chain run (of which writing only useful candidates and ending convex and unchanged
+// waves gave 52 us, the one launch and the cheaper reading 19 us); 13-24% of the
+// nodes change in an iteration and 31-53% of the lines hold one.  5.8M-node 3D mesh,
+// three directions of 20-node lines: 86 us, 100 us before.
+template <typename T, int DD, int CHUNK>
+__global__ __launch_bounds__(4 * kLineThreads) void k_grid_hulls(GridArgs g, const Step* __restrict__ steps, Group grp,
+                                                                int lds_bytes, const T* __restrict__ Win,
+                                                                const uint8_t* __restrict__ ch,
+                                                                T* __restrict__ cand, uint32_t* __restrict__ offs,
+                                                                uint8_t* __restrict__ marks, int mark_bytes) {
+  extern __shared__ __align__(8) unsigned char line_mem[];
+  const LineRef ref = line_of_block(grp, blockIdx.x, threadIdx.x);
+  const int wave = threadIdx.x / kLineThreads;
+  if (wave >= ref.waves) return;                  // waves are independent: no barrier below
+  const Step& s = steps[ref.dir];
+  const bool live = ref.t < s.count;
+  if (!__any(live)) return;
+  int I[9];
+  const uint32_t p = uint32_t(line_start<DD>(g, s, live ? ref.t : s.count - 1, I));
+  const uint32_t ds = uint32_t(s.ds);             // node indices are below 2^31: 32-bit steps wrap correctly
+  const int L = line_length<DD>(g, s, I);         // 3 .. 64
+  bool act = live;
+  if (ch) {
+    uint32_t any = 0;
+    uint32_t node = p;
+    for (int q0 = 0; q0 < L; q0 += CHUNK) {
+#pragma unroll
+      for (int i = 0; i < CHUNK; ++i) {
+        any |= ch[node];
+        node += q0 + i + 1 < L ? ds : 0u;         // the last node again beyond the end
+      }
     }
-    if (!mask || cand1) {
-      cd[p + ds] = val;
-      if (od) od[p + ds] = cand1 ? (1u | (1u << 16)) : 0u;
-      if (mask) atomicOr(mask + p + ds, bit);
-    }
-    return;
+    act = act && any != 0;
+    if (!__any(act)) return;
   }
+  T* const vin = reinterpret_cast<T*>(line_mem + wave * (lds_bytes / ref.waves)) + threadIdx.x % kLineThreads;
+  auto win = [&](int q) -> T { return vin[q * kLineThreads]; };
+  // pop: the first node whose step is not above the one before; gap: an absent value
+  // between present ones (differences across absent ends compare false)
+  int pop = kBitLine, beg = 0;                    // beg: absent values before the first present one
+  bool seen = false, ended = false, gap = false;
+  {
+    T w1 = inf_t<T>(), d1 = T(__builtin_nan(""));
+    uint32_t node = p;
+    for (int q0 = 0; q0 < L; q0 += CHUNK) {
+      T a[CHUNK];                                 // independent loads: one memory round trip
+#pragma unroll
+      for (int i = 0; i < CHUNK; ++i) {
+        a[i] = Win[node];
+        node += q0 + i + 1 < L ? ds : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < CHUNK; ++i) {
+        const int q = q0 + i;
+        const bool in = q < L;
+        const T w = a[i], d = w - w1;
+        const bool f = w < inf_t<T>();
+        if (in) vin[q * kLineThreads] = w;
+        if (in && d1 >= d) pop = min(pop, q);
+        seen = seen || f;
+        beg = seen ? beg : q + 1;
+        gap = gap || (in && f && ended);
+        ended = ended || (!f && seen);
+        w1 = w;
+        d1 = d;
+      }
+    }
+  }
+  act = act && (pop < kBitLine || gap);
+  if (!__any(act)) return;
+  if (!act) return;
+  // from the first pop with the vertices before it (without a gap: nodes beg .. pop - 1),
+  // or from the start
+  int q = gap ? 0 : pop;
+  unsigned long long fin = gap ? 0ull : ((1ull << q) - 1ull) & ~((1ull << beg) - 1ull);   // present nodes
+  unsigned long long hm = fin;                                                            // vertices
+  // the top three vertices, i2 the top (values of fewer vertices are not looked at)
+  int i2 = max(q - 1, 0), i1 = max(q - 2, 0), i0 = max(q - 3, 0);
+  T v2 = win(i2), v1 = win(i1), v0 = win(i0), w = win(q), wn = win(min(q + 1, L - 1));
+  while (q < L) {
+    const bool f = w < inf_t<T>();
+    if (f && (hm & (hm - 1)) && (v2 - v1) * T(q - i2) >= (w - v2) * T(i2 - i1)) {
+      hm &= ~(1ull << i2);
+      i2 = i1;
+      v2 = v1;
+      i1 = i0;
+      v1 = v0;
+      const unsigned long long below = hm & ((1ull << i1) - 1ull);
+      i0 = below ? 63 - __builtin_clzll(below) : 0;
+      v0 = win(i0);
+      continue;
+    }
+    if (f) {
+      fin |= 1ull << q;
+      hm |= 1ull << q;
+      i0 = i1;
+      v0 = v1;
+      i1 = i2;
+      v1 = v2;
+      i2 = q;
+      v2 = w;
+    }
+    ++q;
+    w = wn;
+    wn = win(min(q + 1, L - 1));
+  }
+  // the first and the last finite node are vertices, so every other finite node
+  // that is not one lies inside a segment
+  T* const cd = cand + int64_t(ref.slot) * g.size;
+  for (unsigned long long rest = fin & ~hm; rest; rest &= rest - 1) {
+    const int c = __builtin_ctzll(rest);
+    const int a = 63 - __builtin_clzll(hm & ((1ull << c) - 1ull));
+    const int b = c + __builtin_ctzll(hm >> c);
+    const T val = (T(b - c) * win(a) + T(c - a) * win(b)) / T(b - a);
+    if (val < pick_limit(win(c))) {
+      const uint32_t node = p + uint32_t(c) * ds;
+      cd[node] = val;
+      if (offs) offs[int64_t(ref.slot) * g.size + node] = uint32_t(c - a) | (uint32_t(b - c) << 16);
+      marks[int64_t(node) * mark_bytes + ref.slot] = 1;
+    }
+  }
+}
+
+// Longer lines: the chain's vertices are a stack of offsets in LDS.  STAGED: the
+// values sit in the thread's LDS column; otherwise they are read in place.
+template <typename T, bool STAGED>
+__global__ __launch_bounds__(kLineThreads) void k_grid_hulls_long(GridArgs g, const Step* __restrict__ steps, Group grp,
+                                                                 const T* __restrict__ Win, T* __restrict__ cand,
+                                                                 uint32_t* __restrict__ offs,
+                                                                 uint8_t* __restrict__ marks, int mark_bytes, int len) {
+  extern __shared__ __align__(8) unsigned char line_mem[];
+  const int tid = threadIdx.x;
+  const LineRef ref = line_of_block(grp, blockIdx.x, tid);
+  const Step& s = steps[ref.dir];
+  if (ref.t >= s.count) return;
+  int I[9];
+  const int64_t p = line_start<9>(g, s, ref.t, I);
+  const int64_t ds = s.ds;
+  const int L = line_length<9>(g, s, I);
+  T* const vin = reinterpret_cast<T*>(line_mem) + tid;  // STAGED only
+  uint16_t* const st = reinterpret_cast<uint16_t*>(reinterpret_cast<T*>(line_mem) +
+                                                   (STAGED ? len * kLineThreads : 0)) + tid;
   auto win = [&](int q) -> T { return STAGED ? vin[q * kLineThreads] : Win[p + q * ds]; };
   if constexpr (STAGED) {
-    // chunks of independent loads: a line costs one or two memory round trips, not L
+    // chunks of independent loads: a line costs a few memory round trips, not L
+    constexpr int CHUNK = 32;
     for (int q0 = 0; q0 < L; q0 += CHUNK) {
       T a[CHUNK];
 #pragma unroll
-      for (int i = 0; i < CHUNK; ++i) a[i] = q0 + i < L ? Win[p + (q0 + i) * ds] : T(0);
+      for (int i = 0; i < CHUNK; ++i) a[i] = Win[p + min(q0 + i, L - 1) * ds];
 #pragma unroll
       for (int i = 0; i < CHUNK; ++i)
         if (q0 + i < L) vin[(q0 + i) * kLineThreads] = a[i];
     }
   }
-  // monotone chain: the top vertex is popped while the slope into it is at least
-  // the slope from it to the new point (collinear points are not kept).  One flat
-  // loop of pops and pushes (at most 2L trips), so the lanes of a wave, whose hulls
-  // differ, stay within the longest line's trip count.
   int h = 0, i1 = 0, i2 = 0;
   T v1 = T(0), v2 = T(0);
   {
     int q = 0;
-    T w = L > 0 ? win(0) : T(0);
+    T w = win(0);
     while (q < L) {
       const bool fin = w < inf_t<T>();
       if (fin && h >= 2 && (v2 - v1) * T(q - i2) >= (w - v2) * T(i2 - i1)) {
@@ -193,67 +337,30 @@ __device__ __forceinline__ void hull_line(const T* __restrict__ Win, T* __restri
       if (q < L) w = win(q);
     }
   }
+  if (h < 2) return;
   // candidates along the line, one flat loop; (a, b) is the segment holding q
-  int k = 1, a = 0, b = 0, last = -1;
-  T wa = T(0), wb = T(0);
-  if (h >= 2) {
-    a = st[0];
-    b = st[kLineThreads];
-    wa = win(a);
-    wb = win(b);
-    last = st[(h - 1) * kLineThreads];
-  }
-  for (int q = 0; q < L; ++q) {
-    T val = inf_t<T>();
-    uint32_t off = 0;
-    if (q > a && q < last) {
-      if (q == b) {
-        a = b;
-        wa = wb;
-        ++k;
-        b = st[k * kLineThreads];
-        wb = win(b);
-      } else if (win(q) < inf_t<T>()) {
-        val = (T(b - q) * wa + T(q - a) * wb) / T(b - a);
-        off = uint32_t(q - a) | (uint32_t(b - q) << 16);
-      }
+  T* const cd = cand + int64_t(ref.slot) * g.size;
+  int k = 1, a = st[0], b = st[kLineThreads];
+  T wa = win(a), wb = win(b);
+  const int last = st[(h - 1) * kLineThreads];
+  for (int q = a + 1; q < last; ++q) {
+    if (q == b) {
+      a = b;
+      wa = wb;
+      ++k;
+      b = st[k * kLineThreads];
+      wb = win(b);
+      continue;
     }
-    if (!mask || val < inf_t<T>()) {
-      cd[p + q * ds] = val;
-      if (od) od[p + q * ds] = off;
-      if (mask) atomicOr(mask + p + q * ds, bit);
+    const T own = win(q);
+    if (!(own < inf_t<T>())) continue;
+    const T val = (T(b - q) * wa + T(q - a) * wb) / T(b - a);
+    if (val < pick_limit(own)) {
+      const int64_t node = p + q * ds;
+      cd[node] = val;
+      if (offs) offs[int64_t(ref.slot) * g.size + node] = uint32_t(q - a) | (uint32_t(b - q) << 16);
+      marks[int64_t(node) * mark_bytes + ref.slot] = 1;
     }
-  }
-}
-
-template <typename T, bool STAGED, int R>
-__global__ __launch_bounds__(kLineThreads) void k_grid_hulls(GridArgs g, const Step* __restrict__ steps, Group grp,
-                                                            const T* __restrict__ Win, T* __restrict__ cand,
-                                                            uint32_t* __restrict__ offs, uint32_t* __restrict__ mask,
-                                                            int len) {
-  extern __shared__ __align__(8) unsigned char line_mem[];
-  const int tid = threadIdx.x;
-  const int blk = blockIdx.x;
-  int i = 0;
-#pragma unroll
-  for (int k = 0; k < kGroupMax; ++k) i += (k < grp.n && blk >= grp.block_end[k]) ? 1 : 0;
-  const int j = grp.slot[i];
-  const Step& s = steps[grp.dir[i]];
-  const int64_t t0 = int64_t(blk - (i ? grp.block_end[i - 1] : 0)) * kLineThreads * R + tid;
-  T* const cd = cand + int64_t(j) * g.size;
-  uint32_t* const od = offs ? offs + int64_t(j) * g.size : nullptr;
-  T* const vin = reinterpret_cast<T*>(line_mem) + tid;  // STAGED only
-  uint16_t* const st = reinterpret_cast<uint16_t*>(reinterpret_cast<T*>(line_mem) +
-                                                   (STAGED ? len * kLineThreads : 0)) + tid;
-  constexpr int kChunk = R > 1 ? kShortLine : 32;
-  int I[9];
-  int slab = 0;
-  int64_t p = 0;
-  for (int r = 0; r < R; ++r) {
-    const int64_t t = t0 + int64_t(r) * kLineThreads;
-    if (t >= s.count) break;
-    if (r == 0 || !line_advance(g, s, slab, I, &p, kLineThreads)) p = line_start(g, s, t, I, &slab);
-    hull_line<T, STAGED, kChunk>(Win, cd, od, mask, 1u << j, p, s.ds, line_length(g, s, I), vin, st);
   }
 }
 
@@ -287,13 +394,14 @@ __device__ __forceinline__ uint32_t interior_mask(const GridArgs& g, uint32_t p)
 // running value only when lower by more than 4 units of rounding relative to
 // max(|W|, 1e-3), so directions that tie to rounding leave the node to the first.
 // kFirst: the running value starts from Win (else Wout, and with sel the running
-// laminate) and every node is written.  Sparse (mask): only the marked slots of
-// a node are read, and the mask goes back to 0.
+// laminate) and every node is written.  Only the marked slots of a node are read,
+// and its marks go back to 0.
 // The maximal decrease Win - W over nodes with finite Win goes to *dec (atomic
 // maximum of the non-negative doubles' bit patterns; W only decreases over the
 // groups, so the maximum over the nodes the groups lower is the iteration's).
 // kLast: the node stresses / moduli of the laminate that lowered a node, with the
-// weights of its value (eq. 5.2, first case), or the node's own, go to Pout / Aout.
+// weights of its value (eq. 5.2, first case), or the node's own, go to Pout / Aout;
+// whether the iteration changed the node goes to ch.
 //
 // kNb: some directions have slot -1; the node reads its two neighbours for those.
 // Which of them concern a node depends only on its interior mask, so k_grid_lists
@@ -353,15 +461,32 @@ __global__ __launch_bounds__(64) void k_grid_lists(const PickDir* __restrict__ d
   if (lane == 0) counts[M] = full;
 }
 
-template <typename T, int DD, bool kNb>
+// The node's marks as a bit mask (bit = slot); they go back to 0.
+template <int BYTES>
+__device__ __forceinline__ uint32_t take_marks(uint8_t* marks, int64_t node) {
+  auto bits = [](uint32_t w) { return (w | w >> 7 | w >> 14 | w >> 21) & 15u; };
+  if constexpr (BYTES == 4) {
+    uint32_t* const at = reinterpret_cast<uint32_t*>(marks) + node;
+    const uint32_t w = *at;
+    if (w) *at = 0u;
+    return bits(w);
+  } else {
+    uint4* const at = reinterpret_cast<uint4*>(marks) + node;
+    const uint4 w = *at;
+    if (w.x | w.y | w.z | w.w) *at = make_uint4(0u, 0u, 0u, 0u);
+    return bits(w.x) | bits(w.y) << 4 | bits(w.z) << 8 | bits(w.w) << 12;
+  }
+}
+
+template <typename T, int DD, bool kNb, int BYTES>
 __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const Step* __restrict__ steps,
                                                    const PickDir* __restrict__ dirs, int ne,
                                                    int pitch, const longlong2* __restrict__ lists,
                                                    const int* __restrict__ counts,
                                                    const T* __restrict__ Win, T* __restrict__ Wout,
                                                    const T* __restrict__ cand, const uint32_t* __restrict__ offs,
-                                                   uint32_t* __restrict__ mask, Carry<T> cy, int flags,
-                                                   unsigned long long* dec) {
+                                                   uint8_t* __restrict__ marks, uint8_t* __restrict__ ch,
+                                                   Carry<T> cy, int flags, unsigned long long* dec) {
   const int64_t n = g.size;
   const bool first = flags & kFirst;
   const bool carry = cy.Pout || cy.Aout;
@@ -374,7 +499,7 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const
     const int64_t node = p0 + threadIdx.x;
     const bool live = node < n;
     const T w0 = live ? Win[node] : inf_t<T>();
-    const uint32_t mk = !live ? 0u : mask ? mask[node] : ~0u;
+    const uint32_t mk = live ? take_marks<BYTES>(marks, node) : 0u;
     T cur = first || !live ? w0 : Wout[node];
     int32_t sl = -1;
     uint32_t so = 0;
@@ -384,11 +509,10 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const
     }
     bool changed = false;
     int sslot = -1;                              // candidate slot of the laminate taken here
-    auto limit = [](T w) { return w - T(4) * eps_t<T>() * fmax(fabs(w), T(1e-3)); };
-    T lim = limit(cur);
+    T lim = pick_limit(cur);
     auto take = [&](T c, int dir, int slot) {
       cur = c;
-      lim = limit(c);
+      lim = pick_limit(c);
       sl = dir;
       sslot = slot;
       changed = true;
@@ -427,14 +551,14 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const
       T v[kGroupMax];                            // all loads first, then the ordered choice
 #pragma unroll
       for (int j = 0; j < kGroupMax; ++j)
-        v[j] = j < ne && live && ((mk >> j) & 1u) ? cand[int64_t(j) * n + node] : inf_t<T>();
+        v[j] = (mk >> j) & 1u ? cand[int64_t(j) * n + node] : inf_t<T>();
 #pragma unroll
       for (int j = 0; j < kGroupMax; ++j)
-        if (j < ne && v[j] < lim) take(v[j], dirs[j].dir, j);
+        if (v[j] < lim) take(v[j], dirs[j].dir, j);
     }
     if (!live) continue;
     if (changed) so = sslot < 0 ? 1u | (1u << 16) : offs ? offs[int64_t(sslot) * n + node] : 0u;
-    if (mask && mk) mask[node] = 0u;
+    if (flags & kLast) ch[node] = cur == w0 ? 0 : 1;
     if (first || changed) Wout[node] = cur;
     if (changed && w0 < inf_t<T>()) m = fmax(m, double(w0) - double(cur));
     if (carry && !(flags & kLast) && (first || changed)) {
@@ -561,7 +685,9 @@ struct GridWork {
   int* counts = nullptr;
   T* cand = nullptr;
   uint32_t* offs = nullptr;
-  uint32_t* mask = nullptr;    // sparse mode only
+  uint8_t* marks = nullptr;
+  int mark_bytes = 0;          // per node
+  uint8_t* ch = nullptr;
   int32_t* sel = nullptr;
   uint32_t* soff = nullptr;
 };
@@ -616,48 +742,71 @@ inline void plan_groups(const GridArgs& g, const std::vector<Step>& steps, std::
   }
 }
 
-// One iteration: for each group of directions, the hull launches then the pick launch.
+// One iteration: for each group of directions, the hull launches then the pick
+// launch.  ch: the previous iteration's changed nodes (null on the first).
 template <typename T>
 hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const std::vector<PickDir>& dirs,
                       const std::vector<Segment>& segs, const GridWork<T>& wk, const T* Win,
-                      T* Wout, Carry<T> cy, unsigned long long* dec, hipStream_t st, KTimer* tm) {
+                      const uint8_t* ch, T* Wout, Carry<T> cy, unsigned long long* dec, hipStream_t st, KTimer* tm) {
   const bool carry = cy.Pout || cy.Aout;
   for (size_t sg = 0; sg < segs.size(); ++sg) {
     const Segment& seg = segs[sg];
-    // one hull launch per length class of the group's lines, each with the LDS of
-    // its own longest line (short lines would otherwise run at the occupancy of the
-    // longest); the candidates keep their group slots, so the order is unchanged
-    for (int part = 0; part < kLenClasses; ++part) {
-      const int R = part == 0 ? kShortRun : 1;
+    uint32_t* offs = carry ? wk.offs : nullptr;
+    // the hull directions with lines of at most kBitLine nodes in one launch, then
+    // those of at most 128 (staged) and longer ones
+    for (int part = 0; part < 3; ++part) {
       Group grp{};
-      int blocks = 0, len = 1;
+      int len = 1, main_len = 1;
+      int64_t main_lines = 0;
       for (int j = 0; j < seg.n; ++j) {
         const PickDir& p = dirs[size_t(seg.e0 + j)];
         if (p.slot < 0) continue;
         const Step& s = steps[size_t(p.dir)];
-        if (len_class(s.len) != part) continue;
-        blocks += int(blocks_of(s.count, kLineThreads * R));
+        if ((s.len <= kBitLine ? 0 : s.len <= 128 ? 1 : 2) != part || s.count == 0) continue;
         grp.dir[grp.n] = p.dir;
         grp.slot[grp.n] = p.slot;
-        grp.block_end[grp.n] = blocks;
         ++grp.n;
         len = std::max(len, s.len);
+        int64_t lines = 0;                     // lines of the directions of this length
+        for (int i = 0; i < grp.n; ++i)
+          if (steps[size_t(grp.dir[i])].len == s.len) lines += steps[size_t(grp.dir[i])].count;
+        if (lines > main_lines) {
+          main_lines = lines;
+          main_len = s.len;
+        }
       }
       if (grp.n == 0) continue;
-      const size_t staged = (sizeof(T) + sizeof(uint16_t)) * size_t(kLineThreads) * size_t(len);
-      uint32_t* offs = carry ? wk.offs : nullptr;
-      if (blocks == 0) continue;
+      // LDS of a 4-wave block: the columns of 4 waves of the most frequent length (2 if
+      // that passes 64 KB), or of 2 of the longest if those need more
+      const size_t column = sizeof(T) * size_t(kLineThreads);
+      const int main_waves = column * 4 * size_t(main_len) <= size_t(64) * 1024 ? 4 : 2;
+      const size_t share = column * size_t(std::max(main_waves * main_len, 2 * len));
+      int blocks = 0;
+      for (int i = 0; i < grp.n; ++i) {
+        const Step& s = steps[size_t(grp.dir[i])];
+        grp.waves[i] = part > 0 ? 1 : column * 4 * size_t(s.len) <= share ? 4 : 2;
+        blocks += int(blocks_of(s.count, kLineThreads * grp.waves[i]));
+        grp.block_end[i] = blocks;
+      }
       if (tm) tm->begin("grid_lines", st);
-      if (part == 0)
-        hipLaunchKernelGGL((k_grid_hulls<T, true, kShortRun>), dim3(blocks), dim3(kLineThreads), staged, st, g,
-                           wk.steps, grp, Win, wk.cand, offs, wk.mask, len);
-      else if (staged <= size_t(kStageBytes))
-        hipLaunchKernelGGL((k_grid_hulls<T, true, 1>), dim3(blocks), dim3(kLineThreads), staged, st, g, wk.steps,
-                           grp, Win, wk.cand, offs, wk.mask, len);
-      else
-        hipLaunchKernelGGL((k_grid_hulls<T, false, 1>), dim3(blocks), dim3(kLineThreads),
-                           sizeof(uint16_t) * size_t(kLineThreads) * size_t(len), st, g, wk.steps, grp, Win,
-                           wk.cand, offs, wk.mask, len);
+      if (part == 0) {
+        const auto hulls = g.dd == 4 ? (main_len <= 8    ? k_grid_hulls<T, 4, 8>
+                                        : main_len <= 16 ? k_grid_hulls<T, 4, 16>
+                                        : main_len <= 24 ? k_grid_hulls<T, 4, 24>
+                                                         : k_grid_hulls<T, 4, 32>)
+                                     : (main_len <= 8    ? k_grid_hulls<T, 9, 8>
+                                        : main_len <= 16 ? k_grid_hulls<T, 9, 16>
+                                        : main_len <= 24 ? k_grid_hulls<T, 9, 24>
+                                                         : k_grid_hulls<T, 9, 32>);
+        hipLaunchKernelGGL(hulls, dim3(blocks), dim3(4 * kLineThreads), share, st, g, wk.steps, grp, int(share), Win,
+                           ch, wk.cand, offs, wk.marks, wk.mark_bytes);
+      } else {
+        const size_t stack = sizeof(uint16_t) * size_t(kLineThreads) * size_t(len);
+        const bool staged = part == 1 && column * size_t(len) + stack <= size_t(kStageBytes);
+        const auto hulls = staged ? k_grid_hulls_long<T, true> : k_grid_hulls_long<T, false>;
+        hipLaunchKernelGGL(hulls, dim3(blocks), dim3(kLineThreads), staged ? column * size_t(len) + stack : stack, st,
+                           g, wk.steps, grp, Win, wk.cand, offs, wk.marks, wk.mark_bytes, len);
+      }
       if (tm) tm->end(st);
     }
     const int flags = (sg == 0 ? kFirst : 0) | (sg + 1 == segs.size() ? kLast : 0);
@@ -667,21 +816,25 @@ hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const s
     if (tm) tm->begin("grid_pick", st);
     const unsigned pick_blocks = std::min<unsigned>((blocks_of(g.size, 256) + 7u) & ~7u, kPickBlocks);
     const unsigned strips = (blocks_of(g.size, 256) + pick_blocks - 1) / pick_blocks;   // of 256 nodes, per block
-    const auto pick = g.dd == 4 ? (seg.neighbours ? k_grid_pick<T, 4, true> : k_grid_pick<T, 4, false>)
-                                : (seg.neighbours ? k_grid_pick<T, 9, true> : k_grid_pick<T, 9, false>);
+    const bool m4 = wk.mark_bytes == 4;
+    const auto pick =
+        g.dd == 4 ? (seg.neighbours ? (m4 ? k_grid_pick<T, 4, true, 4> : k_grid_pick<T, 4, true, 16>)
+                                    : (m4 ? k_grid_pick<T, 4, false, 4> : k_grid_pick<T, 4, false, 16>))
+                  : (seg.neighbours ? (m4 ? k_grid_pick<T, 9, true, 4> : k_grid_pick<T, 9, true, 16>)
+                                    : (m4 ? k_grid_pick<T, 9, false, 4> : k_grid_pick<T, 9, false, 16>));
     hipLaunchKernelGGL(pick, dim3(pick_blocks), dim3(256), 0, st, g, int(strips), wk.steps, wk.dirs + seg.e0, seg.n,
                        seg.pitch, reinterpret_cast<const longlong2*>(wk.lists + seg.list0),
-                       wk.counts + (int64_t(sg) << g.dd), Win, Wout, wk.cand, carry ? wk.offs : nullptr, wk.mask, c,
-                       flags, dec);
+                       wk.counts + (int64_t(sg) << g.dd), Win, Wout, wk.cand, carry ? wk.offs : nullptr, wk.marks,
+                       wk.ch, c, flags, dec);
     if (tm) tm->end(st);
   }
   return hipGetLastError();
 }
 
-// steps enumerate every line (dense) or the lines of at least 3 nodes (sparse).
+// steps enumerate the lines of at least 3 nodes.
 template <typename T>
-r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step>& steps, bool sparse, T* W, T* P,
-                          T* A, int k_max, double tol, int32_t* iterations, double* decrease, hipStream_t st) {
+r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step>& steps, T* W, T* P, T* A,
+                          int k_max, double tol, int32_t* iterations, double* decrease, hipStream_t st) {
   const size_t n = size_t(g.size);
   const bool carry = P || A;
   std::vector<PickDir> dirs;
@@ -692,7 +845,8 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
   size_t list_len = 0;
   for (const Segment& sg : segs)
     if (sg.neighbours) list_len = size_t(sg.list0) + (size_t(sg.pitch) << g.dd);
-  const size_t sizes[13] = {round256(sizeof(T) * n),
+  const int mark_bytes = G <= 4 ? 4 : kGroupMax;
+  const size_t sizes[14] = {round256(sizeof(T) * n),
                            P ? round256(sizeof(T) * n * size_t(g.dd)) : 0,
                            A ? round256(sizeof(T) * n * size_t(g.dd * g.dd)) : 0,
                            round256(sizeof(unsigned long long) * size_t(k_max)),
@@ -701,10 +855,11 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
                            carry ? round256(sizeof(uint32_t) * n * size_t(G)) : 0,
                            carry ? round256(sizeof(int32_t) * n) : 0,
                            carry ? round256(sizeof(uint32_t) * n) : 0,
-                           sparse ? round256(sizeof(uint32_t) * n) : 0,
+                           round256(size_t(mark_bytes) * n),
                            round256(sizeof(PickDir) * std::max<size_t>(dirs.size(), 1)),
                            list_len ? round256(sizeof(long long) * list_len) : 0,
-                           list_len ? round256(sizeof(int) * (segs.size() << g.dd)) : 0};
+                           list_len ? round256(sizeof(int) * (segs.size() << g.dd)) : 0,
+                           round256(n)};
   size_t total = 0;
   for (size_t b : sizes) total += b;
   void* base = nullptr;
@@ -726,17 +881,20 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
   wk.offs = static_cast<uint32_t*>(take(6));
   wk.sel = static_cast<int32_t*>(take(7));
   wk.soff = static_cast<uint32_t*>(take(8));
-  wk.mask = static_cast<uint32_t*>(take(9));
+  wk.marks = static_cast<uint8_t*>(take(9));
+  wk.mark_bytes = mark_bytes;
   wk.dirs = static_cast<PickDir*>(take(10));
   wk.lists = static_cast<long long*>(take(11));
   wk.counts = static_cast<int*>(take(12));
+  wk.ch = static_cast<uint8_t*>(take(13));
   hipError_t e = hipMemcpyAsync(wk.steps, steps.data(), sizeof(Step) * steps.size(), hipMemcpyHostToDevice, st);
   if (e == hipSuccess && !dirs.empty())
     e = hipMemcpyAsync(wk.dirs, dirs.data(), sizeof(PickDir) * dirs.size(), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return r1h::fail(h, e, "grid steps");
-  if (sparse)  // the invariant the sparse launches keep: no marks between groups
-    hipLaunchKernelGGL((k_grid_fill<uint32_t>), dim3(blocks_of(int64_t(n), 256)), dim3(256), 0, st, int64_t(n),
-                       wk.mask, 0u);
+  // the invariant the pick launches keep: no marks between groups
+  const int64_t words = int64_t(n) * (mark_bytes / 4);
+  hipLaunchKernelGGL((k_grid_fill<uint32_t>), dim3(blocks_of(words, 256)), dim3(256), 0, st, words,
+                     reinterpret_cast<uint32_t*>(wk.marks), 0u);
   hipLaunchKernelGGL(k_grid_zero, dim3(blocks_of(k_max, 256)), dim3(256), 0, st, wk.dec, k_max);
   for (size_t k = 0; k < segs.size(); ++k)
     if (segs[k].neighbours)
@@ -752,7 +910,7 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
   int k = 0;
   while (k < k_max) {
     Carry<T> cy{pcur, pnxt, acur, anxt, nullptr, nullptr};
-    e = grid_sweep<T>(g, steps, dirs, segs, wk, cur, nxt, cy, wk.dec + k, st, tm);
+    e = grid_sweep<T>(g, steps, dirs, segs, wk, cur, k ? wk.ch : nullptr, nxt, cy, wk.dec + k, st, tm);
     unsigned long long bits = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&bits, wk.dec + k, sizeof(bits), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -892,32 +1050,14 @@ r1_status r1_grid_laminate(r1_handle h, const r1_grid* grid, int32_t n_dir, cons
     }
     if (zero) return R1_EINVAL;
   }
-  // sparse when the lines of at least 3 nodes -- the only ones that can lower a
-  // node -- of the directions with hull launches cover under half of those
-  // direction-node pairs (4-D meshes and the long directions of the paper's 9-D
-  // mesh: nearly all)
-  double covered = 0.0;
-  int hulls = 0;
-  for (int m = 0; m < n_dir; ++m) {
-    Step t = st_list[m];
-    step_slabs(g, &t, 1);
-    if (t.len < 3 || by_neighbours(g, t)) continue;
-    ++hulls;
-    for (int len = 3; len <= kGridMaxLen; ++len) {
-      step_slabs(g, &t, len);
-      if (t.count == 0) break;
-      covered += double(t.count) * (len == 3 ? 3.0 : 1.0);
-    }
-  }
-  const bool sparse = covered < 0.5 * double(hulls) * double(g.size);
-  for (int m = 0; m < n_dir; ++m) step_slabs(g, &st_list[m], sparse ? 3 : 1);
+  for (int m = 0; m < n_dir; ++m) step_slabs(g, &st_list[m], 3);
   hipError_t e = hipSetDevice(h->device);
   if (e != hipSuccess) return r1h::fail(h, e, "hipSetDevice");
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dtype == R1_F32)
-    return grid_laminate_T<float>(h, g, st_list, sparse, static_cast<float*>(W), static_cast<float*>(P),
+    return grid_laminate_T<float>(h, g, st_list, static_cast<float*>(W), static_cast<float*>(P),
                                   static_cast<float*>(A), k_max, tol, iterations, decrease, st);
-  return grid_laminate_T<double>(h, g, st_list, sparse, static_cast<double*>(W), static_cast<double*>(P),
+  return grid_laminate_T<double>(h, g, st_list, static_cast<double*>(W), static_cast<double*>(P),
                                  static_cast<double*>(A), k_max, tol, iterations, decrease, st);
 }
 

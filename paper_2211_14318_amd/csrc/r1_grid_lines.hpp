@@ -119,20 +119,21 @@ inline void step_slabs(const GridArgs& g, Step* s, int min_len = 1) {
 
 // Node index (and multi-index I, first dd entries) of line start t, 0 <= t < s.count
 // (< 2^31, so the mixed-radix decoding runs in 32-bit arithmetic); *slab receives
-// the slab of t.
+// the slab of t.  DD >= dd: components looked at (dd where known at compile time).
+template <int DD = 9>
 __host__ __device__ inline int64_t line_start(const GridArgs& g, const Step& s, int64_t t, int* I,
                                               int* slab = nullptr) {
   int c = 0;
 #pragma unroll
-  for (int k = 0; k < 9; ++k) c += t >= s.slab_end[k] ? 1 : 0;
+  for (int k = 0; k < DD; ++k) c += t >= s.slab_end[k] ? 1 : 0;
   int64_t r64 = t;
 #pragma unroll
-  for (int k = 1; k < 9; ++k)
+  for (int k = 1; k < DD; ++k)
     if (k == c) r64 -= s.slab_end[k - 1];
   uint32_t r = uint32_t(r64);
   int64_t p = 0;
 #pragma unroll
-  for (int k = 8; k >= 0; --k) {
+  for (int k = DD - 1; k >= 0; --k) {
     if (k < g.dd) {
       const int lo = k < c ? s.lo[k] : (k == c ? s.slo[k] : s.flo[k]);
       const uint32_t w = uint32_t(k < c ? s.hi[k] - s.lo[k] : (k == c ? s.shi[k] - s.slo[k] : s.fhi[k] - s.flo[k]));
@@ -166,12 +167,14 @@ __host__ __device__ inline bool line_advance(const GridArgs& g, const Step& s, i
   return delta == 0;
 }
 
-// Nodes of the line that starts at multi-index I.
+// Nodes of the line that starts at multi-index I (DD as in line_start).
+template <int DD = 9>
 __host__ __device__ inline int line_length(const GridArgs& g, const Step& s, const int* I) {
   int L = kGridMaxLen;
-  for (int c = 0; c < g.dd; ++c) {
+#pragma unroll
+  for (int c = 0; c < DD; ++c) {
     const int v = s.s[c];
-    if (v == 0) continue;
+    if (c >= g.dd || v == 0) continue;
     const int room = v > 0 ? g.n[c] - 1 - I[c] : I[c];     // steps left inside the box
     const int a = v > 0 ? v : -v;
     L = std::min(L, (a == 1 ? room : room / a) + 1);

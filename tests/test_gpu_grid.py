@@ -176,6 +176,39 @@ def test_grid_every_hull_path_on_random_values(lib, kind, n):
 
 
 @pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("n", [(8, 9, 16, 5), (17, 24, 25, 2), (32, 33, 3, 2), (64, 65, 2, 4), (4, 1, 1, 57)])
+def test_grid_line_lengths_over_iterations(lib, kind, n):
+    """Lines on both sides of every length class (8, 16, 24, 32, 64 nodes), mixed in one
+    launch, with absent values at their ends and between present ones, over three
+    iterations of one call (after the first, lines without a changed node are skipped):
+    every iterate's maximal decrease and the last iterate equal the oracle's sweeps."""
+    r1, h, torch = lib
+    dt = torch.float64 if kind == "f64" else torch.float32
+    g, og = both_grids(r1, 2, n, (0.5, -0.2, -0.3, 0.7), 0.05)
+    N = O.grid_size(og)
+    rng = np.random.default_rng(sum(n))
+    ax = np.meshgrid(*[np.linspace(-1.0, 1.0, k) if k > 1 else np.zeros(1) for k in n], indexing="ij")
+    W0 = sum(x * x for x in ax).ravel()               # convex: lowered around the perturbed nodes only
+    at = rng.random(N) < 0.03
+    W0[at] += rng.normal(size=at.sum())
+    W0[rng.random(N) < 0.02] = np.inf
+    W = torch.tensor(W0, dtype=dt, device="cuda")
+    ref = W.double().cpu().numpy()
+    hist = h.grid_laminate(g, r1.grid_r11(2), W, k_max=3, tol=0.0)
+    decs = []
+    while len(decs) < len(hist):
+        ref, md = O.grid_sweep(og, O.grid_r11(2), ref)
+        decs.append(md)
+    Wg = W.double().cpu().numpy()
+    fin = np.isfinite(ref)
+    # three roundings of values up to 4 per iteration and margin
+    tol = 3 * (4 * 4 + 3) * 4 * (2.0 ** -52 if kind == "f64" else 2.0 ** -23)
+    assert np.array_equal(np.isfinite(Wg), fin)
+    assert np.max(np.abs(Wg[fin] - ref[fin])) <= tol
+    assert np.max(np.abs(np.array(hist) - decs)) <= tol
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
 @pytest.mark.parametrize("dim,n", [(2, (3, 4, 3, 21)), (3, (4, 4, 2, 3, 4, 4, 2, 3, 4))])
 def test_grid_neighbour_directions_on_random_values(lib, kind, dim, n):
     """Directions with lines of at most three nodes (candidates formed from a node's two
