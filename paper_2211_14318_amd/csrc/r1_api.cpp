@@ -176,6 +176,22 @@ r1_status r1h::scratch(r1_handle h, size_t bytes, void** p) {
   return R1_OK;
 }
 
+r1_status r1h::readback(r1_handle h, double** words, hipEvent_t** ready) {
+  if (!h->readback) {
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < 2 && e == hipSuccess; ++i)
+      if (!h->readback_ready[i]) e = hipEventCreateWithFlags(&h->readback_ready[i], hipEventDisableTiming);
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&h->readback), 2 * sizeof(double), hipHostMallocDefault);
+    if (e != hipSuccess) {
+      h->readback = nullptr;
+      return fail(h, e, "readback buffer");
+    }
+  }
+  *words = h->readback;
+  *ready = h->readback_ready;
+  return R1_OK;
+}
+
 // Samples per lane K for a segment of S lanes: the smallest power of two with
 // S*K/2 >= c (one sample pair per offset on each side of the centre); for 16
 // lanes also 14, which fits lines of 193..225 samples (the 201-sample ones)
@@ -231,6 +247,9 @@ r1_status r1_destroy(r1_handle h) {
   (void)h->timer.collect();
   for (auto& kv : h->dirs) (void)hipFree(kv.second);
   if (h->scratch) (void)hipFree(h->scratch);
+  if (h->readback) (void)hipHostFree(h->readback);
+  for (hipEvent_t ev : h->readback_ready)
+    if (ev) (void)hipEventDestroy(ev);
   r1h::release_batched(h);
   delete h;
   return R1_OK;

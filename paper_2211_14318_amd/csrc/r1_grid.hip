@@ -32,6 +32,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "r1.h"
@@ -108,6 +109,17 @@ __global__ __launch_bounds__(256) void k_grid_energy(GridArgs g, r1d::Material m
 constexpr int kGroupMax = 16;
 constexpr int kBitLine = 64;   // lines of at most this many nodes keep their hull as a bit mask
 
+// Ends an iteration's launches when the iteration before met the tolerance (its
+// maximal decrease is at prev; null: no iteration before): an iteration is enqueued
+// before the host has read the one before, and must then do nothing.
+struct Guard {
+  const unsigned long long* prev;
+  double tol;
+  __device__ __forceinline__ bool stop() const {
+    return prev && __longlong_as_double((long long)(*prev)) <= tol;
+  }
+};
+
 struct Group {
   int n;                       // directions of this launch ...
   int dir[kGroupMax];          // ... their indices
@@ -159,11 +171,12 @@ __device__ __forceinline__ LineRef line_of_block(const Group& grp, int blk, int 
 // three directions of 20-node lines: 86 us, 100 us before.
 template <typename T, int DD, int CHUNK>
 __global__ __launch_bounds__(4 * kLineThreads) void k_grid_hulls(GridArgs g, const Step* __restrict__ steps, Group grp,
-                                                                int lds_bytes, const T* __restrict__ Win,
+                                                                Guard guard, int lds_bytes, const T* __restrict__ Win,
                                                                 const uint8_t* __restrict__ ch,
                                                                 T* __restrict__ cand, uint32_t* __restrict__ offs,
                                                                 uint8_t* __restrict__ marks, int mark_bytes) {
   extern __shared__ __align__(8) unsigned char line_mem[];
+  if (guard.stop()) return;
   const LineRef ref = line_of_block(grp, blockIdx.x, threadIdx.x);
   const int wave = threadIdx.x / kLineThreads;
   if (wave >= ref.waves) return;                  // waves are independent: no barrier below
@@ -280,11 +293,12 @@ __global__ __launch_bounds__(4 * kLineThreads) void k_grid_hulls(GridArgs g, con
 // values sit in the thread's LDS column; otherwise they are read in place.
 template <typename T, bool STAGED>
 __global__ __launch_bounds__(kLineThreads) void k_grid_hulls_long(GridArgs g, const Step* __restrict__ steps, Group grp,
-                                                                 const T* __restrict__ Win, T* __restrict__ cand,
+                                                                 Guard guard, const T* __restrict__ Win, T* __restrict__ cand,
                                                                  uint32_t* __restrict__ offs,
                                                                  uint8_t* __restrict__ marks, int mark_bytes, int len) {
   extern __shared__ __align__(8) unsigned char line_mem[];
   const int tid = threadIdx.x;
+  if (guard.stop()) return;
   const LineRef ref = line_of_block(grp, blockIdx.x, tid);
   const Step& s = steps[ref.dir];
   if (ref.t >= s.count) return;
@@ -479,7 +493,8 @@ __device__ __forceinline__ uint32_t take_marks(uint8_t* marks, int64_t node) {
 }
 
 template <typename T, int DD, bool kNb, int BYTES>
-__global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const Step* __restrict__ steps,
+__global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, Guard guard, int strips,
+                                                   const Step* __restrict__ steps,
                                                    const PickDir* __restrict__ dirs, int ne,
                                                    int pitch, const longlong2* __restrict__ lists,
                                                    const int* __restrict__ counts,
@@ -487,6 +502,7 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const
                                                    const T* __restrict__ cand, const uint32_t* __restrict__ offs,
                                                    uint8_t* __restrict__ marks, uint8_t* __restrict__ ch,
                                                    Carry<T> cy, int flags, unsigned long long* dec) {
+  if (guard.stop()) return;
   const int64_t n = g.size;
   const bool first = flags & kFirst;
   const bool carry = cy.Pout || cy.Aout;
@@ -596,15 +612,9 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, int strips, const
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_grid_fill(int64_t n, T* a, T v) {
+__global__ __launch_bounds__(256) void k_grid_zero(int64_t n, uint32_t* a) {
   const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) a[i] = v;
-}
-
-__global__ __launch_bounds__(256) void k_grid_zero(unsigned long long* dec, int n) {
-  const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
-  if (i < n) dec[i] = 0ull;
+  if (i < n) a[i] = 0u;
 }
 
 // Multilinear interpolation of the node values at n points F (SoA, d*d x n):
@@ -743,11 +753,13 @@ inline void plan_groups(const GridArgs& g, const std::vector<Step>& steps, std::
 }
 
 // One iteration: for each group of directions, the hull launches then the pick
-// launch.  ch: the previous iteration's changed nodes (null on the first).
+// launch.  ch: the previous iteration's changed nodes (null on the first); guard:
+// whether there is anything left to do.
 template <typename T>
 hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const std::vector<PickDir>& dirs,
                       const std::vector<Segment>& segs, const GridWork<T>& wk, const T* Win,
-                      const uint8_t* ch, T* Wout, Carry<T> cy, unsigned long long* dec, hipStream_t st, KTimer* tm) {
+                      const uint8_t* ch, T* Wout, Carry<T> cy, Guard guard, unsigned long long* dec, hipStream_t st,
+                      KTimer* tm) {
   const bool carry = cy.Pout || cy.Aout;
   for (size_t sg = 0; sg < segs.size(); ++sg) {
     const Segment& seg = segs[sg];
@@ -798,14 +810,14 @@ hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const s
                                         : main_len <= 16 ? k_grid_hulls<T, 9, 16>
                                         : main_len <= 24 ? k_grid_hulls<T, 9, 24>
                                                          : k_grid_hulls<T, 9, 32>);
-        hipLaunchKernelGGL(hulls, dim3(blocks), dim3(4 * kLineThreads), share, st, g, wk.steps, grp, int(share), Win,
+        hipLaunchKernelGGL(hulls, dim3(blocks), dim3(4 * kLineThreads), share, st, g, wk.steps, grp, guard, int(share), Win,
                            ch, wk.cand, offs, wk.marks, wk.mark_bytes);
       } else {
         const size_t stack = sizeof(uint16_t) * size_t(kLineThreads) * size_t(len);
         const bool staged = part == 1 && column * size_t(len) + stack <= size_t(kStageBytes);
         const auto hulls = staged ? k_grid_hulls_long<T, true> : k_grid_hulls_long<T, false>;
         hipLaunchKernelGGL(hulls, dim3(blocks), dim3(kLineThreads), staged ? column * size_t(len) + stack : stack, st,
-                           g, wk.steps, grp, Win, wk.cand, offs, wk.marks, wk.mark_bytes, len);
+                           g, wk.steps, grp, guard, Win, wk.cand, offs, wk.marks, wk.mark_bytes, len);
       }
       if (tm) tm->end(st);
     }
@@ -822,7 +834,7 @@ hipError_t grid_sweep(const GridArgs& g, const std::vector<Step>& steps, const s
                                     : (m4 ? k_grid_pick<T, 4, false, 4> : k_grid_pick<T, 4, false, 16>))
                   : (seg.neighbours ? (m4 ? k_grid_pick<T, 9, true, 4> : k_grid_pick<T, 9, true, 16>)
                                     : (m4 ? k_grid_pick<T, 9, false, 4> : k_grid_pick<T, 9, false, 16>));
-    hipLaunchKernelGGL(pick, dim3(pick_blocks), dim3(256), 0, st, g, int(strips), wk.steps, wk.dirs + seg.e0, seg.n,
+    hipLaunchKernelGGL(pick, dim3(pick_blocks), dim3(256), 0, st, g, guard, int(strips), wk.steps, wk.dirs + seg.e0, seg.n,
                        seg.pitch, reinterpret_cast<const longlong2*>(wk.lists + seg.list0),
                        wk.counts + (int64_t(sg) << g.dd), Win, Wout, wk.cand, carry ? wk.offs : nullptr, wk.marks,
                        wk.ch, c, flags, dec);
@@ -846,90 +858,99 @@ r1_status grid_laminate_T(r1_handle h, const GridArgs& g, const std::vector<Step
   for (const Segment& sg : segs)
     if (sg.neighbours) list_len = size_t(sg.list0) + (size_t(sg.pitch) << g.dd);
   const int mark_bytes = G <= 4 ? 4 : kGroupMax;
-  const size_t sizes[14] = {round256(sizeof(T) * n),
-                           P ? round256(sizeof(T) * n * size_t(g.dd)) : 0,
-                           A ? round256(sizeof(T) * n * size_t(g.dd * g.dd)) : 0,
-                           round256(sizeof(unsigned long long) * size_t(k_max)),
-                           round256(sizeof(Step) * steps.size()),
-                           round256(sizeof(T) * n * size_t(G)),
-                           carry ? round256(sizeof(uint32_t) * n * size_t(G)) : 0,
-                           carry ? round256(sizeof(int32_t) * n) : 0,
-                           carry ? round256(sizeof(uint32_t) * n) : 0,
-                           round256(size_t(mark_bytes) * n),
-                           round256(sizeof(PickDir) * std::max<size_t>(dirs.size(), 1)),
-                           list_len ? round256(sizeof(long long) * list_len) : 0,
-                           list_len ? round256(sizeof(int) * (segs.size() << g.dd)) : 0,
-                           round256(n)};
+  const size_t step_bytes = round256(sizeof(Step) * steps.size());
+  const size_t dir_bytes = round256(sizeof(PickDir) * std::max<size_t>(dirs.size(), 1));
+  const size_t dec_bytes = round256(sizeof(unsigned long long) * size_t(k_max));
+  const size_t mark_total = round256(size_t(mark_bytes) * n);
   size_t total = 0;
-  for (size_t b : sizes) total += b;
+  auto place = [&](size_t bytes) { return std::exchange(total, total + round256(bytes)); };
+  const size_t at_tables = place(step_bytes + dir_bytes), at_zeros = place(dec_bytes + mark_total),
+               at_w2 = place(sizeof(T) * n), at_p2 = place(P ? sizeof(T) * n * size_t(g.dd) : 0),
+               at_a2 = place(A ? sizeof(T) * n * size_t(g.dd * g.dd) : 0), at_cand = place(sizeof(T) * n * size_t(G)),
+               at_offs = place(carry ? sizeof(uint32_t) * n * size_t(G) : 0),
+               at_sel = place(carry ? sizeof(int32_t) * n : 0), at_soff = place(carry ? sizeof(uint32_t) * n : 0),
+               at_lists = place(sizeof(long long) * list_len),
+               at_counts = place(list_len ? sizeof(int) * (segs.size() << g.dd) : 0), at_ch = place(n);
   void* base = nullptr;
   r1_status s = r1h::scratch(h, total, &base);
   if (s) return s;
-  char* at = static_cast<char*>(base);
-  auto take = [&](int i) -> void* {
-    void* q = sizes[i] ? at : nullptr;
-    at += sizes[i];
-    return q;
-  };
+  auto at = [&](size_t off) -> void* { return static_cast<char*>(base) + off; };
   GridWork<T> wk;
-  wk.W2 = static_cast<T*>(take(0));
-  wk.P2 = static_cast<T*>(take(1));
-  wk.A2 = static_cast<T*>(take(2));
-  wk.dec = static_cast<unsigned long long*>(take(3));
-  wk.steps = static_cast<Step*>(take(4));
-  wk.cand = static_cast<T*>(take(5));
-  wk.offs = static_cast<uint32_t*>(take(6));
-  wk.sel = static_cast<int32_t*>(take(7));
-  wk.soff = static_cast<uint32_t*>(take(8));
-  wk.marks = static_cast<uint8_t*>(take(9));
+  wk.steps = static_cast<Step*>(at(at_tables));
+  wk.dirs = static_cast<PickDir*>(at(at_tables + step_bytes));
+  wk.dec = static_cast<unsigned long long*>(at(at_zeros));
+  wk.marks = static_cast<uint8_t*>(at(at_zeros + dec_bytes));
   wk.mark_bytes = mark_bytes;
-  wk.dirs = static_cast<PickDir*>(take(10));
-  wk.lists = static_cast<long long*>(take(11));
-  wk.counts = static_cast<int*>(take(12));
-  wk.ch = static_cast<uint8_t*>(take(13));
-  hipError_t e = hipMemcpyAsync(wk.steps, steps.data(), sizeof(Step) * steps.size(), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && !dirs.empty())
-    e = hipMemcpyAsync(wk.dirs, dirs.data(), sizeof(PickDir) * dirs.size(), hipMemcpyHostToDevice, st);
+  wk.W2 = static_cast<T*>(at(at_w2));
+  wk.P2 = P ? static_cast<T*>(at(at_p2)) : nullptr;
+  wk.A2 = A ? static_cast<T*>(at(at_a2)) : nullptr;
+  wk.cand = static_cast<T*>(at(at_cand));
+  wk.offs = static_cast<uint32_t*>(at(at_offs));
+  wk.sel = static_cast<int32_t*>(at(at_sel));
+  wk.soff = static_cast<uint32_t*>(at(at_soff));
+  wk.lists = static_cast<long long*>(at(at_lists));
+  wk.counts = static_cast<int*>(at(at_counts));
+  wk.ch = static_cast<uint8_t*>(at(at_ch));
+  std::vector<char> tables(step_bytes + dir_bytes);
+  std::memcpy(tables.data(), steps.data(), sizeof(Step) * steps.size());
+  if (!dirs.empty()) std::memcpy(tables.data() + step_bytes, dirs.data(), sizeof(PickDir) * dirs.size());
+  hipError_t e = hipMemcpyAsync(wk.steps, tables.data(), tables.size(), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return r1h::fail(h, e, "grid steps");
-  // the invariant the pick launches keep: no marks between groups
-  const int64_t words = int64_t(n) * (mark_bytes / 4);
-  hipLaunchKernelGGL((k_grid_fill<uint32_t>), dim3(blocks_of(words, 256)), dim3(256), 0, st, words,
-                     reinterpret_cast<uint32_t*>(wk.marks), 0u);
-  hipLaunchKernelGGL(k_grid_zero, dim3(blocks_of(k_max, 256)), dim3(256), 0, st, wk.dec, k_max);
+  // the decreases, and the marks (the invariant the pick launches keep: none between groups)
+  const int64_t words = int64_t((dec_bytes + mark_total) / 4);
+  hipLaunchKernelGGL(k_grid_zero, dim3(blocks_of(words, 256)), dim3(256), 0, st, words,
+                     static_cast<uint32_t*>(at(at_zeros)));
   for (size_t k = 0; k < segs.size(); ++k)
     if (segs[k].neighbours)
       hipLaunchKernelGGL(k_grid_lists, dim3(1u << g.dd), dim3(64), 0, st, wk.dirs + segs[k].e0, segs[k].n,
                          segs[k].pitch, wk.lists + segs[k].list0, wk.counts + (int64_t(k) << g.dd));
   KTimer* tm = h->timer.on ? &h->timer : nullptr;
-  T* cur = W;
-  T* nxt = wk.W2;
-  T* pcur = P;
-  T* pnxt = wk.P2;
-  T* acur = A;
-  T* anxt = wk.A2;
-  int k = 0;
-  while (k < k_max) {
-    Carry<T> cy{pcur, pnxt, acur, anxt, nullptr, nullptr};
-    e = grid_sweep<T>(g, steps, dirs, segs, wk, cur, k ? wk.ch : nullptr, nxt, cy, wk.dec + k, st, tm);
-    unsigned long long bits = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&bits, wk.dec + k, sizeof(bits), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return r1h::fail(h, e, "grid iteration");
-    double md;
-    std::memcpy(&md, &bits, sizeof(md));
+  double* seen = nullptr;                      // two pinned words for the decreases read back ...
+  hipEvent_t* ready = nullptr;                 // ... and the events after their copies
+  s = r1h::readback(h, &seen, &ready);
+  if (s) return s;
+  // iteration i reads the iterate in W (even i) or W2 (odd i) and writes the other
+  auto enqueue = [&](int i) -> hipError_t {
+    const bool odd = i & 1;
+    Carry<T> cy{odd ? wk.P2 : P, odd ? P : wk.P2, odd ? wk.A2 : A, odd ? A : wk.A2, nullptr, nullptr};
+    const Guard guard{i ? wk.dec + (i - 1) : nullptr, tol};
+    hipError_t r = grid_sweep<T>(g, steps, dirs, segs, wk, odd ? wk.W2 : W, i ? wk.ch : nullptr, odd ? W : wk.W2, cy,
+                                 guard, wk.dec + i, st, tm);
+    if (r == hipSuccess) r = hipMemcpyAsync(seen + (i & 1), wk.dec + i, sizeof(double), hipMemcpyDeviceToHost, st);
+    if (r == hipSuccess) r = hipEventRecord(ready[i & 1], st);
+    return r;
+  };
+  // one iteration ahead of the host's reading of the decreases, so that the device
+  // does not wait for the host between iterations (with launch timing on, none ahead:
+  // an iteration that turns out to be one too many would count as launches)
+  const int ahead = tm ? 1 : 2;
+  int k = 0, queued = 0;
+  for (;;) {
+    while (queued < k_max && queued - k < ahead) {
+      e = enqueue(queued);
+      if (e != hipSuccess) break;
+      ++queued;
+    }
+    if (e == hipSuccess) e = hipEventSynchronize(ready[k & 1]);
+    if (e != hipSuccess) {
+      (void)hipStreamSynchronize(st);          // nothing of this call stays in flight
+      return r1h::fail(h, e, "grid iteration");
+    }
+    const double md = seen[k & 1];
     if (decrease) decrease[k] = md;
     ++k;
-    std::swap(cur, nxt);
-    std::swap(pcur, pnxt);
-    std::swap(acur, anxt);
-    if (md <= tol) break;
+    if (md <= tol || k == k_max) break;
   }
-  if (cur != W) {
-    e = hipMemcpyAsync(W, cur, sizeof(T) * n, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess && P) e = hipMemcpyAsync(P, pcur, sizeof(T) * n * size_t(g.dd), hipMemcpyDeviceToDevice, st);
+  if (k & 1) {
+    e = hipMemcpyAsync(W, wk.W2, sizeof(T) * n, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess && P)
+      e = hipMemcpyAsync(P, wk.P2, sizeof(T) * n * size_t(g.dd), hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess && A)
-      e = hipMemcpyAsync(A, acur, sizeof(T) * n * size_t(g.dd * g.dd), hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+      e = hipMemcpyAsync(A, wk.A2, sizeof(T) * n * size_t(g.dd * g.dd), hipMemcpyDeviceToDevice, st);
+  }
+  if ((k & 1) || queued > k) {                 // the workspace is the handle's: leave nothing using it
+    const hipError_t e2 = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = e2;
     if (e != hipSuccess) return r1h::fail(h, e, "grid copy");
   }
   if (iterations) *iterations = k;

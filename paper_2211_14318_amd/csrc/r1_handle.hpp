@@ -26,6 +26,8 @@ struct r1_handle_s {
   KTimer timer;                            // optional per-kernel event timing
   hipStream_t capture_stream = nullptr;    // private stream for graph capture
   uint64_t plan_serial = 0;
+  double* readback = nullptr;              // two pinned host words and their events (r1_grid_laminate)
+  hipEvent_t readback_ready[2] = {nullptr, nullptr};
   void* noalloc = nullptr;                 // device address of the fixed workspace (r1_envelope_stress_noalloc)
 };
 
@@ -37,6 +39,8 @@ r1_status check_lamination(const r1_lamination* lam);
 void level_meta(const r1_level& lv, int dim, r1d::Level* out);
 r1_status device_levels(r1_handle h, const r1_level* const* lv, int count, int dim, r1d::Level* out);
 r1_status scratch(r1_handle h, size_t bytes, void** p);
+// Two pinned host doubles with an event each, made on first use and kept by the handle.
+r1_status readback(r1_handle h, double** words, hipEvent_t** ready);
 int samples_per_lane(int S, int n_t);
 int batch_samples_per_lane(int S, int n_t);
 // Roles of a level's lines for the segment width: lines of a one-level
