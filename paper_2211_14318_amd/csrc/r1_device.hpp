@@ -864,6 +864,13 @@ __device__ __forceinline__ bool near_tie(const Env<T>& e) {
   return (e.mp + e.mq) > 0 && e.second - e.h <= tie_margin<T>() * fmax(fabs(e.h), tie_floor<T>());
 }
 
+// A line provider with a member fill(m0) is told before the directions from m0 on
+// are asked for (see LineTable).
+template <typename F>
+__device__ __forceinline__ auto lines_from(F& f, int m0, int) -> decltype(f.fill(m0)) { return f.fill(m0); }
+template <typename F>
+__device__ __forceinline__ void lines_from(F&, int, long) {}
+
 // One lamination level at a point (wave-uniform): min over the level's n_dir
 // directions of the line hulls at the centre.  wc = W at the point;
 // line_fn(dir) returns the coefficients of W along direction dir.  warm
@@ -880,13 +887,15 @@ __device__ __forceinline__ bool near_tie(const Env<T>& e) {
 // lines needing a bridge search share wavefronts; ties in the minimum go to the
 // smaller direction index whatever the visiting order.  centre (optional): the
 // coefficients of the lines at t = 0 (J0, c0; the rest unused), when the caller
-// has them at hand; else line_fn(0) is taken.  Every lane of the wave must call
-// it.
+// has them at hand; else line_fn(0) is taken.  from, step (multiples of the lines a
+// wave takes at once): the wave takes the directions from, from + step, .. only
+// (several waves may share a point).  Every lane of the wave must call it.  The
+// result's values are in the hull form; envelope_finish maps them back.
 template <typename T, int S, int K, int M = kFamNH, typename LineFn>
-__device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay,
-                                 LineFn line_fn, T* warm = nullptr, T c2u = T(__builtin_nan("")),
-                                 int* order = nullptr, const Line<T>* centre = nullptr) {
-  constexpr int NSEG = kWave / S;
+__device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay,
+                                LineFn line_fn, T* warm = nullptr, T c2u = T(__builtin_nan("")),
+                                int* order = nullptr, const Line<T>* centre = nullptr, int from = 0,
+                                int step = kWave / S) {
   constexpr int H = K / 2;
   const int lane = threadIdx.x & (kWave - 1);
   const int seg = lane / S;
@@ -931,7 +940,8 @@ __device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layou
     }
   }
   Env<T> best = {inf_v<T>(), 0, 0, 0, 0, inf_v<T>()};
-  for (int m0 = 0; m0 < n_dir; m0 += NSEG) {
+  for (int m0 = from; m0 < n_dir; m0 += step) {
+    lines_from(line_fn, m0, 0);
     const bool act = m0 + seg < n_dir;
     const int dir = order ? order[act ? m0 + seg : n_dir - 1] : (act ? m0 + seg : n_dir - 1);
     Line<T> L = line_fn(dir);
@@ -1017,11 +1027,54 @@ __device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layou
     best.mq = take ? oq : best.mq;
     best.capped |= oc;
   }
-  if (scaled) {   // back from the hull form; a centre that is a vertex is W there, exactly
+  return best;
+}
+
+// envelope_scan's result mapped back from the hull form (the damage energies); a
+// centre that is a vertex is W there (wc), exactly.
+template <typename T, int M>
+__device__ __forceinline__ Env<T> envelope_finish(const Point<T>& q, T wc, Env<T> best) {
+  if (M == kFamSTVK || q.model == 0) {
     best.h = (best.mp + best.mq) ? fma(best.h, q.sc, q.B) : wc;
     best.second = fma(best.second, q.sc, q.B);
   }
   return best;
+}
+
+// One lamination level at a point by one wave, all directions.
+template <typename T, int S, int K, int M = kFamNH, typename LineFn>
+__device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay,
+                                 LineFn line_fn, T* warm = nullptr, T c2u = T(__builtin_nan("")),
+                                 int* order = nullptr, const Line<T>* centre = nullptr) {
+  return envelope_finish<T, M>(q, wc, envelope_scan<T, S, K, M>(q, wc, n_dir, lay, line_fn, warm, c2u, order, centre));
+}
+
+
+// Line coefficients of one wave's directions in LDS: what differs between the lines
+// through a point (J1, c1, c2, or c1 .. c4 for St. Venant-Kirchhoff).
+constexpr int kTabLines = 256;
+template <typename T, int M>
+struct LineTable {
+  T v[M == kFamSTVK ? 4 : 3][kTabLines];
+  __device__ __forceinline__ void put(int e, const Line<T>& L) {
+    if constexpr (M == kFamSTVK) {
+      v[0][e] = L.c1; v[1][e] = L.c2; v[2][e] = L.c3; v[3][e] = L.c4;
+    } else {
+      v[0][e] = L.J1; v[1][e] = L.c1; v[2][e] = L.c2;
+    }
+  }
+  // the rest (J0, c0) from c, a line through the point
+  __device__ __forceinline__ Line<T> get(int e, const Line<T>& c) const {
+    if constexpr (M == kFamSTVK) return Line<T>{c.J0, c.J1, c.c0, v[0][e], v[1][e], v[2][e], v[3][e]};
+    return Line<T>{c.J0, v[0][e], c.c0, v[1][e], v[2][e], T(0), T(0)};
+  }
+};
+
+// Orders a wave's own LDS writes before its later reads (waves of a block share no
+// table, so no barrier).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // One lamination level at a point with the lines set up from its geometry g

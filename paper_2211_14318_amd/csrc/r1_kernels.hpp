@@ -2,7 +2,8 @@
 // r1_kernels_<dtype>_<dim>d.hip units instantiate them.
 //
 //   k_depth1    one wavefront per point: W^1 (and its laminate stress) -- the
-//               min over directions of the line hulls at the centre.
+//               min over directions of the line hulls at the centre;
+//               k_depth1_split: several wavefronts per point, for small batches.
 //   k_outer     depth 2, one workgroup per (point, outer direction): the outer
 //               line's samples are inner envelopes W^1(F + t_i R), computed by
 //               the block's waves into LDS; wave 0 then takes the outer hull.
@@ -133,52 +134,80 @@ __device__ __forceinline__ PointSetup<T, D, M> point_setup(const KArgs& a, int64
   return s;
 }
 
-// One-level envelope of point p on level lv from its constants s, with stress,
-// tree and flags as requested by a (wave-level: every lane of the wave calls
-// it).  kDefer: the stress is left to k_stress1, which finds the point's
-// laminate (direction, m_-, m_+) as integers in the first T slot of rows 0, 1,
-// 2 of P.
-template <typename T, int D, int S, int K, int M, bool kDefer = false>
-__device__ __forceinline__ void point_depth1_body(const KArgs& a, int64_t p, const Level& lv,
-                                                  const Layout<T, S, K>& lay, const PointSetup<T, D, M>& s) {
-  if (s.state != 0) {
-    if (lane_id() == 0) write_bad_point<T, D>(a, p, s.state == 1, a.want_stress);
-    return;
-  }
-  const Point<T>& q = s.q;
-  const double* G = s.g.G;
-  const double bn = s.bn;
-  Env<T> e = envelope_geom<T, D, S, K, M>(q, s.g, s.wc, lv, lay);
-  const bool stress = a.want_stress && a.P && !kDefer;
-  if (lane_id() == 0) {
-    static_cast<T*>(a.W)[p] = e.h;
-    if (kDefer && a.want_stress && a.P) {
+// Writes point p's one-level result e (one thread): W, tree and flags as requested
+// by a, and with kDefer its laminate (direction, m_-, m_+) as integers in the first
+// T slot of rows 0, 1, 2 of P, where k_stress1 finds it; else its stress.
+template <typename T, int D, int M, bool kDefer>
+__device__ __forceinline__ void write_depth1(const KArgs& a, int64_t p, const Level& lv, const Point<T>& q,
+                                             const double* G, double bn, const Env<T>& e) {
+  static_cast<T*>(a.W)[p] = e.h;
+  if (a.want_stress && a.P) {
+    if constexpr (kDefer) {
       T* P = static_cast<T*>(a.P);
       *reinterpret_cast<int32_t*>(P + p) = e.dir;
       *reinterpret_cast<int32_t*>(P + a.n + p) = e.mp;
       *reinterpret_cast<int32_t*>(P + 2 * a.n + p) = e.mq;
+    } else {
+      laminate_stress1<T, D, M>(a, p, lv, q, G, bn, e.dir, e.mp, e.mq);
     }
-    const int c = (lv.n_t - 1) / 2;
-    if (stress) laminate_stress1<T, D, M>(a, p, lv, q, G, bn, e.dir, e.mp, e.mq);
-    if (a.tree) {
-      float xi = (e.mp + e.mq) ? float(double(e.mp) / double(e.mp + e.mq)) : 1.0f;
-      a.tree[p * R1_TREE_NODES] = r1_laminate{e.dir, c - e.mp, c + e.mq, xi};
-      for (int k = 1; k < R1_TREE_NODES; ++k) a.tree[p * R1_TREE_NODES + k] = r1_laminate{0, 0, 0, 1.0f};
-    }
-    if (a.flags) a.flags[p] = (e.capped ? R1_PT_ITERCAP : 0) | (near_tie(e) ? R1_PT_TIE : 0);
   }
+  const int c = (lv.n_t - 1) / 2;
+  if (a.tree) {
+    float xi = (e.mp + e.mq) ? float(double(e.mp) / double(e.mp + e.mq)) : 1.0f;
+    a.tree[p * R1_TREE_NODES] = r1_laminate{e.dir, c - e.mp, c + e.mq, xi};
+    for (int k = 1; k < R1_TREE_NODES; ++k) a.tree[p * R1_TREE_NODES + k] = r1_laminate{0, 0, 0, 1.0f};
+  }
+  if (a.flags) a.flags[p] = (e.capped ? R1_PT_ITERCAP : 0) | (near_tie(e) ? R1_PT_TIE : 0);
 }
 
-// The same with the point's constants formed in place.
-template <typename T, int D, int S, int K, int M, bool kDefer = false>
+// One-level envelope of point p on level lv with stress, tree and flags as
+// requested by a (wave-level: every lane of the wave calls it).
+template <typename T, int D, int S, int K, int M>
 __device__ __forceinline__ void point_depth1(const KArgs& a, int64_t p, const Level& lv) {
-  point_depth1_body<T, D, S, K, M, kDefer>(a, p, lv, make_layout<T, S, K>(lv), point_setup<T, D, M>(a, p));
+  const Layout<T, S, K> lay = make_layout<T, S, K>(lv);
+  const PointSetup<T, D, M> s = point_setup<T, D, M>(a, p);
+  if (s.state != 0) {
+    if (lane_id() == 0) write_bad_point<T, D>(a, p, s.state == 1, a.want_stress);
+    return;
+  }
+  const Env<T> e = envelope_geom<T, D, S, K, M>(s.q, s.g, s.wc, lv, lay);
+  if (lane_id() == 0) write_depth1<T, D, M, false>(a, p, lv, s.q, s.g.G, s.bn, e);
 }
+
+// The coefficients of the line through a point along direction dir of lv.
+template <typename T, int D, int M>
+__device__ __forceinline__ Line<T> level_line(const PointSetup<T, D, M>& s, const Level& lv, int dir) {
+  double a[D], b[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) { a[i] = lv.a[dir * D + i]; b[i] = lv.b[dir * D + i]; }
+  return line_of<T, D, M>(s.q, s.g, a, b);
+}
+
+// The lines of a point from its wave's table: entries base .. hold the directions
+// from first on, up to the end of the level or the table (step = 0: the caller has
+// filled in the whole level; else every step directions the table is refilled).
+template <typename T, int D, int M>
+struct TableLines {
+  const PointSetup<T, D, M>& s;
+  const Level& lv;
+  LineTable<T, M>& tab;
+  Line<T> c;                   // J0, c0
+  int base, first, step;
+  __device__ __forceinline__ Line<T> operator()(int dir) const { return tab.get(base + dir - first, c); }
+  __device__ __forceinline__ void fill(int m0) {
+    if (step == 0 || m0 % step != 0) return;     // wave-uniform
+    first = m0;
+    wave_lds_fence();                            // reads of the entries before are done
+    for (int m = lane_id(); m < step && m0 + m < lv.n_dir; m += kWave) tab.put(m, level_line<T, D, M>(s, lv, m0 + m));
+    wave_lds_fence();
+  }
+};
 
 // One-level launch: a block of 4 waves takes a.pts_per_wave (<= kPointsPerWave)
 // points per wave.  Their constants are formed by one thread per point into LDS
-// first (a point's FP64 set-up then costs a lane, not a wavefront), then each
-// wave laminates its points one after the other.
+// first (a point's FP64 set-up then costs a lane, not a wavefront), then the
+// coefficients of their lines by one lane per (point, direction) into the wave's
+// table, then each wave laminates its points one after the other.
 constexpr int kPointsPerWave = 8;
 constexpr int kPointsPerBlock = 4 * kPointsPerWave;
 
@@ -192,23 +221,112 @@ inline int one_level_points_per_wave(int64_t n) {
 template <typename T, int D, int S, int K, int M>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? ((D == 2 && M == kFamNH && K <= 14) ? 4 : K <= 16 ? 3 : 1) : 1) void k_depth1(KArgs a) {
   __shared__ PointSetup<T, D, M> ps[kPointsPerBlock];
+  __shared__ LineTable<T, M> tabs[4];
   const int per_block = 4 * a.pts_per_wave;
   const int64_t p0 = int64_t(blockIdx.x) * per_block;
   if (int(threadIdx.x) < per_block && p0 + threadIdx.x < a.n) ps[threadIdx.x] = point_setup<T, D, M>(a, p0 + threadIdx.x);
   __syncthreads();
   const Layout<T, S, K> lay = make_layout<T, S, K>(a.lv0);
   const int wave = threadIdx.x / kWave;
+  LineTable<T, M>& tab = tabs[wave];
+  // few directions: the lines of all of the wave's points at once; else a point's,
+  // kTabLines at a time
+  const int n_dir = a.lv0.n_dir;
+  const bool whole = n_dir * a.pts_per_wave <= kTabLines;
+  if (whole) {
+    for (int e = lane_id(); e < n_dir * a.pts_per_wave; e += kWave) {
+      const int i = e / n_dir, slot = i * 4 + wave;
+      if (p0 + slot < a.n) tab.put(e, level_line<T, D, M>(ps[slot], a.lv0, e - i * n_dir));
+    }
+    wave_lds_fence();
+  }
   for (int i = 0; i < a.pts_per_wave; ++i) {
     const int slot = i * 4 + wave;
     const int64_t p = p0 + slot;
     if (p >= a.n) break;                      // wave-uniform
-    point_depth1_body<T, D, S, K, M, true>(a, p, a.lv0, lay, ps[slot]);
+    const PointSetup<T, D, M>& s = ps[slot];
+    if (s.state != 0) {
+      if (lane_id() == 0) write_bad_point<T, D>(a, p, s.state == 1, a.want_stress);
+      continue;
+    }
+    TableLines<T, D, M> lines{s, a.lv0, tab, level_line<T, D, M>(s, a.lv0, 0), whole ? i * n_dir : 0, 0,
+                              whole ? 0 : kTabLines};
+    const Env<T> e = envelope_lines<T, S, K, M>(s.q, s.wc, n_dir, lay, lines, nullptr, T(s.q.kq * a.lv0.ab2), nullptr,
+                                                &lines.c);
+    if (lane_id() == 0) write_depth1<T, D, M, true>(a, p, a.lv0, s.q, s.g.G, s.bn, e);
   }
+}
+
+// Few points: a block of up to kSplitWaves waves takes one point, each wave a share
+// of its directions, so that a batch that would leave most of the chip idle behind
+// one wave's serial loop of lines per point (64 points x 16 directions: 35 us on 64
+// waves) spreads over it.  Each wave forms the point's constants by itself (the
+// latency of one lane's set-up, no barrier); the waves' minima meet in LDS in the
+// order of the one-wave scan (value, then direction), so the result is the same;
+// one thread then takes the stress (laminate_stress1, as k_stress1 does).
+constexpr int kSplitWaves = 8;
+
+template <typename T, int D, int S, int K, int M>
+__global__ __launch_bounds__(kWave * kSplitWaves) void k_depth1_split(KArgs a) {
+  __shared__ Env<T> part[kSplitWaves];
+  const int64_t p = blockIdx.x;
+  const int wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
+  const Level& lv = a.lv0;
+  const PointSetup<T, D, M> s = point_setup<T, D, M>(a, p);
+  if (s.state != 0) {                            // the same in every wave
+    if (threadIdx.x == 0) write_bad_point<T, D>(a, p, s.state == 1, a.want_stress);
+    return;
+  }
+  constexpr int NSEG = kWave / S;
+  const Layout<T, S, K> lay = make_layout<T, S, K>(lv);
+  const Line<T> c = level_line<T, D, M>(s, lv, 0);
+  Env<T> e = envelope_scan<T, S, K, M>(s.q, s.wc, lv.n_dir, lay, [&](int dd) { return level_line<T, D, M>(s, lv, dd); },
+                                       nullptr, T(s.q.kq * lv.ab2), nullptr, &c, wave * NSEG, waves * NSEG);
+  if (lane_id() == 0) part[wave] = e;
+  __syncthreads();
+  if (wave != 0) return;
+  e = part[0];
+  for (int w = 1; w < waves; ++w) {
+    const Env<T> o = part[w];
+    const bool take = o.h < e.h || (o.h == e.h && o.dir < e.dir);
+    const T second = take ? fmin(o.second, e.h) : fmin(e.second, o.h);
+    const int capped = e.capped | o.capped;
+    if (take) e = o;
+    e.second = second;
+    e.capped = capped;
+  }
+  e = envelope_finish<T, M>(s.q, s.wc, e);
+  if (threadIdx.x == 0) write_depth1<T, D, M, false>(a, p, lv, s.q, s.g.G, s.bn, e);
+}
+
+// Waves per point of a one-level launch of n points: 1 (k_depth1) or 2 .. kSplitWaves
+// (k_depth1_split).  A wave's time is its line steps (steps / w) and about 1.25 steps
+// of set-up, for every round of waves the chip holds at once, and half a step count of
+// tail where there are several rounds; w minimises that.  Measured (us; w = 1, 2, 4, 8;
+// * the choice), FP64 2D 16 x 201: 64 points 41 23 15 13*, 512: 41 28 20* 25, 2048: 53*
+// 54 61 87; FP64 3D 64 x 257: 64: 107 60 35 31*, 1024: 120 85* 91 109; FP32 3D 256 x 513:
+// 128: 143 78 43 36*, 1024: 147 113 110* 132; FP32 2D 128 x 1025: 4096: 415 399 363* 395.
+// Beyond kSplitPoints the chip is full and k_depth1's shared set-up wins.
+constexpr int64_t kSplitPoints = 8192;
+inline int one_level_waves(int64_t n, int n_dir, int lines_at_once, int resident) {
+  if (n > kSplitPoints) return 1;
+  const int steps = (n_dir + lines_at_once - 1) / lines_at_once;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int w = 1; w <= kSplitWaves && w <= steps; w *= 2) {
+    const double own = double(steps) / w, rounds = double(n) * w / resident;
+    const double cost = rounds > 1.0 ? rounds * (own + 1.25) + 0.5 * own : own + 1.25;
+    if (w == 1 || cost < best_cost) {
+      best = w;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 // Laminate stress of the one-level points (eq. 5.2 on the one-level tree of
 // Algorithm 3: P = xi P0(F+) + (1 - xi) P0(F-)), one thread per point, after
-// k_depth1: it reads the laminate k_depth1 left in P (see point_depth1) and
+// k_depth1: it reads the laminate k_depth1 left in P (see write_depth1) and
 // overwrites it with the stress.  Points k_depth1 found bad (W NaN or +inf)
 // already hold NaN stresses.
 template <typename T, int D, int M>
@@ -598,11 +716,18 @@ hipError_t launch_T(const KArgs& a, int depth, hipStream_t st, KTimer* tm) {
   dim3 blk(256);
   unsigned per = 256 / kWave;
   const int ppw = one_level_points_per_wave(a.n);
+  const int resident = sizeof(T) == 4 && K <= 16 ? 4096 : 2048;   // waves the chip holds at 4 / 2 per SIMD
   const dim3 grd1(unsigned((a.n + 4 * ppw - 1) / (4 * ppw)));
   if (depth == 1) {
     KArgs a1 = a;
     a1.pts_per_wave = ppw;
+    const int wpp = one_level_waves(a.n, a.lv0.n_dir, kWave / S, resident);
     if (tm) tm->begin("depth1", st);
+    if (wpp > 1) {
+      hipLaunchKernelGGL((k_depth1_split<T, D, S, K, M>), dim3(unsigned(a.n)), dim3(kWave * wpp), 0, st, a);
+      if (tm) tm->end(st);
+      return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_depth1<T, D, S, K, M>), grd1, blk, 0, st, a1);
     if (a.want_stress && a.P)
       hipLaunchKernelGGL((k_stress1<T, D, M>), dim3(unsigned((a.n + 255) / 256)), blk, 0, st, a);
@@ -619,8 +744,12 @@ hipError_t launch_T(const KArgs& a, int depth, hipStream_t st, KTimer* tm) {
   pre.want_stress = 0;
   pre.pts_per_wave = ppw;
   dim3 grd(unsigned((a.n + per - 1) / per));
+  const int wpp = one_level_waves(a.n, a.lv1.n_dir, kWave / S, resident);
   if (tm) tm->begin("depth2_centre", st);
-  hipLaunchKernelGGL((k_depth1<T, D, S, K, M>), grd1, blk, 0, st, pre);
+  if (wpp > 1)
+    hipLaunchKernelGGL((k_depth1_split<T, D, S, K, M>), dim3(unsigned(a.n)), dim3(kWave * wpp), 0, st, pre);
+  else
+    hipLaunchKernelGGL((k_depth1<T, D, S, K, M>), grd1, blk, 0, st, pre);
   if (tm) tm->end(st);
   size_t lds = outer_lds_bytes<T>(a.lv0, a.lv1, M);
   dim3 grd_o(unsigned(a.n * a.lv0.n_dir));

@@ -251,3 +251,33 @@ def test_one_level_result_independent_of_batch(lib):
             assert np.array_equal(g["P"], full["P"][:, start:start + m], equal_nan=True), (kind, start, m)
             assert np.array_equal(g["tree"], full["tree"][start:start + m]), (kind, start, m)
             assert np.array_equal(g["flags"], full["flags"][start:start + m]), (kind, start, m)
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,model,dirs,nt", [(2, 0, (1, 1), 65), (2, 0, (5, 7), 201), (2, 0, (17, 16), 33),
+                                               (2, 1, (3, 3), 65), (2, 2, (19, 15), 65), (3, 0, (18, 17), 33),
+                                               (3, 2, (4, 4), 129)])
+def test_few_and_many_points_give_the_same_bits(lib, kind, dim, model, dirs, nt):
+    """A small batch (several waves per point) and the same points repeated to a large one
+    (a wave per point, lines from the wave's table; more than 256 directions refill it), with
+    a non-finite and (neo-Hooke) an inadmissible point: the same values, stresses, trees and
+    flags, and the oracle's energies."""
+    cfg = WL.small_random(dim, 37, dirs, nt, sigma=0.3 if dim == 2 else 0.2, seed_tag=930 + dim)
+    if model == 1:
+        cfg["levels"][0]["a"][:] = np.eye(dim)[0]     # the double well's direction among skew ones
+    F, bn = cfg["F"].copy(), cfg["beta_n"].copy()
+    F[0, 3] = np.nan
+    F[0, 5] = -F[0, 5]
+    few = run_gpu(lib, dict(cfg, F=F, beta_n=bn), kind, model=model)
+    reps = 8200 // 37 + 1
+    many = run_gpu(lib, dict(cfg, F=np.tile(F, (1, reps)), beta_n=np.tile(bn, reps)), kind, model=model)
+    for k in ("W", "P", "flags", "tree"):
+        a = few[k]
+        b = many[k]
+        for r in (0, reps - 1):
+            c = b[:, 37 * r:37 * (r + 1)] if k == "P" else b[37 * r:37 * (r + 1)]
+            assert np.array_equal(a, c, equal_nan=k in ("W", "P")), (k, r)
+    ok = np.ones(37, bool)
+    ok[[3, 5]] = False
+    _, _, W, _, _ = run_oracle(cfg, few["F_in"][:, ok].copy(), few["bn_in"][ok].copy(), model, want_tree=False)
+    assert PA.energy_errors(few["W"][ok], W, kind).max() <= PA.RTOL[kind]
