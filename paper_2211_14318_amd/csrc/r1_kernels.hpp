@@ -218,8 +218,19 @@ inline int one_level_points_per_wave(int64_t n) {
   return int(q < 1 ? 1 : (q > kPointsPerWave ? kPointsPerWave : q));
 }
 
+// Registers: FP32 as measured per variant; FP64 lines of up to 8 samples per lane at
+// three waves per SIMD (168 registers, 8 bytes spilled; 183 and two waves left free,
+// where the logarithm's dependent chains leave issue slots empty: 500,000 points
+// 16 x 201 7.05 -> 6.10 ms, 95,464 points 128 x 221 10.34 -> 9.28 ms, 3D 68,910 points
+// 256 x 113 7.04 -> 6.46 ms).
+template <typename T, int K, int D, int M>
+constexpr int depth1_waves() {
+  if (sizeof(T) == 8) return K <= 8 ? 3 : 1;
+  return (D == 2 && M == kFamNH && K <= 14) ? 4 : K <= 16 ? 3 : 1;
+}
+
 template <typename T, int D, int S, int K, int M>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? ((D == 2 && M == kFamNH && K <= 14) ? 4 : K <= 16 ? 3 : 1) : 1) void k_depth1(KArgs a) {
+__global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KArgs a) {
   __shared__ PointSetup<T, D, M> ps[kPointsPerBlock];
   __shared__ LineTable<T, M> tabs[4];
   const int per_block = 4 * a.pts_per_wave;
