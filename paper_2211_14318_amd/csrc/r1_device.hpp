@@ -37,13 +37,15 @@ template <> __device__ __forceinline__ float inf_v<float>() { return __builtin_i
 template <> __device__ __forceinline__ double inf_v<double>() { return __builtin_inf(); }
 
 // Logarithm used by W: FP32 takes the hardware log2 (v_log_f32) and carries
-// ln 2 in the coefficients; FP64 takes the natural log of r1_math.hpp.
+// ln 2 in the coefficients; FP64 takes the natural log of r1_math.hpp (NaN where
+// det <= 0, as the sample is then).
 __device__ __forceinline__ float lg_t(float x) { return __builtin_amdgcn_logf(x); }
-__device__ __forceinline__ double lg_t(double x) { return r1x::log_f64(x); }
-// Exponential of an argument pre-scaled by the per-point constant kexp:
-// FP32 uses the hardware exp2 (kexp carries log2 e), FP64 the exp of r1_math.hpp.
+__device__ __forceinline__ double lg_t(double x) { return r1x::log_pos(x); }
+// Exponential of an argument pre-scaled by the per-point constant kexp, a minimum
+// with the finite k beta_n and so never NaN: FP32 uses the hardware exp2 (kexp
+// carries log2 e), FP64 the exp of r1_math.hpp.
 __device__ __forceinline__ float expk(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ double expk(double x) { return r1x::exp_f64(x); }
+__device__ __forceinline__ double expk(double x) { return r1x::exp_core(fmax(x, -746.0)); }
 
 struct Material {
   int dim, model;        // model: 0 neo-Hooke damage, 1 double-well test energy, 2 St. Venant-Kirchhoff damage

@@ -16,9 +16,19 @@
 //           e^r by its Taylor polynomial of degree 13 (truncation below 2^-57),
 //           then 2^k by ldexp.
 //
-// Special values follow the C library: log of 0 is -inf, of a negative number
-// or NaN is NaN, of +inf is +inf; exp of -inf (and below -746) is 0, of NaN is
-// NaN.  exp is meant for arguments below 709 (the sampling path passes v <= 0).
+// The reduction's quotient is the correctly rounded one on both sides: an IEEE
+// division on the host, and on the device the hardware reciprocal (2^-23 at worst)
+// with one Newton step (2^-46) and Markstein's residual correction, whose error
+// before the last rounding is the square of that -- no scaling, since the operands'
+// exponents need none.
+//
+// log_f64 and exp_f64 follow the C library on special values: log of 0 is -inf, of
+// a negative number or NaN is NaN, of +inf is +inf; exp of -inf (and below -746) is
+// 0, of NaN is NaN.  exp is meant for arguments below 709 (the sampling path passes
+// v <= 0).  The sampling path itself uses the cores: log_pos (NaN at and below 0 and
+// for +inf, where a sample is absent either way) and exp_core (arguments already
+// clamped at -746), without the selects the special values cost (about a sixth of
+// the two functions).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -32,14 +42,26 @@ constexpr double kLn2Hi = 0x1.62e42feep-1;
 constexpr double kLn2Lo = 0x1.a39ef35793c76p-33;
 constexpr double kLog2e = 0x1.71547652b82fep+0;
 
-__host__ __device__ inline double log_f64(double x) {
+// n / d for d in [1, 4) and |n| < 1 either 0 or at least 2^-60.
+__host__ __device__ inline double near_one_quotient(double n, double d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double y = __builtin_amdgcn_rcp(d);
+  y = std::fma(std::fma(-d, y, 1.0), y, y);
+  const double q = n * y;
+  return std::fma(std::fma(-d, q, n), y, q);
+#else
+  return n / d;
+#endif
+}
+
+// log x for finite x > 0; NaN for +inf and NaN.  (x <= 0: no meaning.)
+__host__ __device__ inline double log_core(double x) {
   int e;
-  double m = std::frexp(x, &e);                       // x = m 2^e, m in [0.5, 1)
+  const double m = std::frexp(x, &e);                 // x = m 2^e, m in [0.5, 1)
   const bool low = m < 0x1.6a09e667f3bcdp-1;          // sqrt(1/2)
-  m = low ? m + m : m;
   e = low ? e - 1 : e;
-  const double f = m - 1.0;
-  const double s = f / (2.0 + f);
+  const double f = std::fma(m, low ? 2.0 : 1.0, -1.0);   // exact: m or 2m, minus 1
+  const double s = near_one_quotient(f, 2.0 + f);
   const double z = s * s;
   // R(z) = sum_{k=1..9} 2 z^k / (2k + 1), coefficients 2/19 .. 2/3 (rounded to nearest)
   double R = 0x1.af286bca1af28p-4;
@@ -54,13 +76,20 @@ __host__ __device__ inline double log_f64(double x) {
   R = R * z;
   const double lm = std::fma(-s, f - R, f);           // log m
   const double de = double(e);
-  const double r = std::fma(de, kLn2Hi, std::fma(de, kLn2Lo, lm));
-  const double inf = __builtin_huge_val();
-  return (x > 0.0 && x < inf) ? r : (x == 0.0 ? -inf : (x == inf ? inf : __builtin_nan("")));
+  return std::fma(de, kLn2Hi, std::fma(de, kLn2Lo, lm));
 }
 
-__host__ __device__ inline double exp_f64(double v) {
-  const double w = v < -746.0 ? -746.0 : v;           // below: the result underflows to 0; NaN stays NaN
+// The select is on the argument: on the result, the compiler branches around the
+// core, which keeps neighbouring samples' dependent chains from overlapping.
+__host__ __device__ inline double log_pos(double x) { return log_core(x > 0.0 ? x : __builtin_nan("")); }
+
+__host__ __device__ inline double log_f64(double x) {
+  const double inf = __builtin_huge_val();
+  return (x > 0.0 && x < inf) ? log_core(x) : (x == 0.0 ? -inf : (x == inf ? inf : __builtin_nan("")));
+}
+
+// exp w for -746 <= w < 709; NaN for NaN.
+__host__ __device__ inline double exp_core(double w) {
   const double k = std::rint(w * kLog2e);
   double r = std::fma(-k, kLn2Hi, w);
   r = std::fma(-k, kLn2Lo, r);
@@ -80,6 +109,10 @@ __host__ __device__ inline double exp_f64(double v) {
   p = std::fma(p, r, 1.0);
   p = std::fma(p, r, 1.0);
   return std::ldexp(p, int(k));
+}
+
+__host__ __device__ inline double exp_f64(double v) {
+  return exp_core(v < -746.0 ? -746.0 : v);           // below: the result underflows to 0; NaN stays NaN
 }
 
 }  // namespace r1x
