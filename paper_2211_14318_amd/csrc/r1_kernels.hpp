@@ -487,6 +487,7 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
   int* order = reinterpret_cast<int*>(wr + co);             // kOuterWaves * n_dir_i (lds_lines)
   __shared__ int capped_any;
   __shared__ T centre;
+  __shared__ double sF[D * D], sR[D * D];     // F and R where the samples read them (not in registers)
   double F[D * D], bn;
   load_point<T, D>(a, p, F, bn);
   double R[D * D];
@@ -494,7 +495,12 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
   for (int i = 0; i < D; ++i)
 #pragma unroll
     for (int j = 0; j < D; ++j) R[i * D + j] = lo.a[mo * D + i] * lo.b[mo * D + j];
-  if (threadIdx.x == 0) { capped_any = 0; centre = w1f; }
+  if (threadIdx.x == 0) {
+    capped_any = 0;
+    centre = w1f;
+#pragma unroll
+    for (int k = 0; k < D * D; ++k) { sF[k] = F[k]; sR[k] = R[k]; }
+  }
   if (tab) {
     if constexpr (M == kFamSTVK) {
       const double k = line_scale<T, M>(a.mat);
@@ -539,7 +545,7 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
     double t = (s & 1) ? t_of(lo, m) : -t_of(lo, m);
     double G[D * D];
 #pragma unroll
-    for (int k = 0; k < D * D; ++k) G[k] = F[k] + t * R[k];
+    for (int k = 0; k < D * D; ++k) G[k] = sF[k] + t * sR[k];
     T v;
     if (tab) {
       if constexpr (M == kFamSTVK) {
@@ -623,8 +629,21 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
   return cv;
 }
 
+// Waves per SIMD k_outer is held to.  FP64 lines of up to 8 samples per lane at three
+// (168 registers; 231 and two left free) where a wave takes few lines at once: what
+// spills then is the per-sample part of log and exp, reloaded once per outer sample,
+// which 32-lane lines (2 at once: 16 and more wave steps per outer sample) make up for
+// and 8-lane lines (8 at once) do not.  40 points, 32 x 513 outer, 16 inner directions,
+// two / three waves: 2D 257 inner points (32 lanes) 9.3 / 8.5 ms, 129 (16 lanes) 4.5 /
+// 4.8, 61 (8 lanes) 2.6 / 3.3; 3D 12.3 / 9.6, 6.4 / 5.9, 3.7 / 4.7.
+template <typename T, int D, int S, int K>
+constexpr int outer_waves() {
+  if (sizeof(T) == 8) return K > 8 ? 1 : (S >= 32 || (S == 16 && D == 3)) ? 3 : 2;
+  return D == 2 && K <= 16 ? 3 : 1;
+}
+
 template <typename T, int D, int S, int K, int M>
-__global__ __launch_bounds__(256, (sizeof(T) == 4 && D == 2 && K <= 16) ? 3 : 1) void k_outer(KArgs a) {
+__global__ __launch_bounds__(256, (outer_waves<T, D, S, K>())) void k_outer(KArgs a) {
   extern __shared__ char smem_raw[];
   const int n_dir_o = a.lv0.n_dir;
   const int64_t p = int64_t(blockIdx.x) / n_dir_o;
