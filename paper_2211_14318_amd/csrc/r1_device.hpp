@@ -866,38 +866,167 @@ __device__ __forceinline__ bool near_tie(const Env<T>& e) {
   return (e.mp + e.mq) > 0 && e.second - e.h <= tie_margin<T>() * fmax(fabs(e.h), tie_floor<T>());
 }
 
-// A line provider with a member fill(m0) is told before the directions from m0 on
-// are asked for (see LineTable).
-template <typename F>
-__device__ __forceinline__ auto lines_from(F& f, int m0, int) -> decltype(f.fill(m0)) { return f.fill(m0); }
-template <typename F>
-__device__ __forceinline__ void lines_from(F&, int, long) {}
+template <typename T>
+__device__ __forceinline__ Env<T> env_none() { return {inf_v<T>(), 0, 0, 0, 0, inf_v<T>()}; }
 
-// One lamination level at a point (wave-uniform): min over the level's n_dir
-// directions of the line hulls at the centre.  wc = W at the point;
-// line_fn(dir) returns the coefficients of W along direction dir.  warm
-// (optional, 2 n_dir entries owned by this wave) carries each direction's
-// bridge slope at the last call (warm[dir]) and at the call before
-// (warm[n_dir + dir]) to the next, whose bridge search starts from their linear
-// extrapolation (from the last slope alone when the one before is absent): NaN
-// for none; callers whose successive points are close and evenly spaced pass
-// it.  c2u: when every
-// line has the same c2 (and, being lines through one point, the same c0), that
-// c2; the polynomial part c0 + c2 t^2 is then formed once per point (NaN: not
-// uniform).  order (optional with warm, n_dir entries owned by this wave): the
-// directions are visited with those that had a bridge last time first, so that
-// lines needing a bridge search share wavefronts; ties in the minimum go to the
-// smaller direction index whatever the visiting order.  centre (optional): the
-// coefficients of the lines at t = 0 (J0, c0; the rest unused), when the caller
-// has them at hand; else line_fn(0) is taken.  from, step (multiples of the lines a
-// wave takes at once): the wave takes the directions from, from + step, .. only
-// (several waves may share a point).  Every lane of the wave must call it.  The
-// result's values are in the hull form; envelope_finish maps them back.
+// Merges another set of directions' result into a (lexicographic in value, direction).
+template <typename T>
+__device__ __forceinline__ void env_merge(Env<T>& a, const Env<T>& o) {
+  const bool take = o.h < a.h || (o.h == a.h && o.dir < a.dir);
+  a.second = take ? fmin(o.second, a.h) : fmin(a.second, o.h);
+  a.capped |= o.capped;
+  if (take) { a.h = o.h; a.dir = o.dir; a.mp = o.mp; a.mq = o.mq; }
+}
+
+// Lines that need no sampling (neo-Hooke damage).  W = w(psi0) with w increasing and
+// concave, and psi0 is strongly convex along a rank-one line: its second derivative is
+// mu |a|^2 |b|^2 + (J1/J)^2 (mu + lambda (1 - ln J)) >= m = mu |a|^2 |b|^2 as long as
+// ln J <= 1 + mu/lambda.  With p = psi0'(0), every sample lies on or above
+// w(psi0 + p t + m t^2/2), so the centre is a hull vertex if that curve lies above w's
+// tangent w(psi0) + w' p t at every |t| of the grid.  At one t the slopes p for which it
+// does form an interval around 0 (the gap is concave in p), whose ends are known: above
+// beta_n w'' decays like e^{-psi0/D0} and the gap is w' m t^2/2 - D_inf D0 e0 g(d), with
+// g(d) = d - 1 + e^{-d} and d D0 = p t + m t^2/2; below beta_n w is linear.  The least
+// end over the grid, both signs of t, is one bound on |p| for all lines through the
+// point: a few operations per line instead of n_t samples.
+//
+// The inverses of g are taken from below (fixed points started below them), and the gap
+// must exceed the rounding of the samples and slopes the vertex test would be made on
+// (noise, twice a first-order bound at small |t|, where it counts: the gap grows like
+// t^2; lines whose J changes by more than a quarter over one step are left out), so a
+// proven line is one the test would find a vertex.  Of the lines of the 2D 16 x 201
+// random points 66% are proven (4 -> 1.5 wave steps), of 3D 256 x 513 52% (64 -> 30), of
+// the inner 32 x 257 lines of two-level samples 44% (8 -> 4.8).  The bound costs about
+// 100 issue slots a point, a wave step 300 to 600; it is taken where there is more than
+// one step.  1,000,000 2D points 2044 -> 1594 us, 262,144 3D points 18.4 -> 11.7 ms, two
+// levels 64 x 1025 / 32 x 257, FP32 96 points 26.5 -> 23.2 ms, FP64 37 points 52.7 -> 41.4.
+template <typename T>
+struct LineProof {
+  T kap;                 // p = c1 + J1 kap, in the units of u
+  float slope, reach;    // proven: |p| <= slope and |J1| <= reach
+  __device__ __forceinline__ bool operator()(const Line<T>& L) const {
+    const T j = L.J1 * kap;
+    const float size = float(fabs(L.c1) + fabs(j));
+    return fma(1e-6f, size, float(fabs(L.c1 + j))) <= slope && float(fabs(L.J1)) <= reach;
+  }
+};
+
+// What the bound needs of a point (line_proof), by one thread or a whole wave alike:
+// psi0 / D0 is written z (-u ln 2 in FP32), and divisions by D0 and the scale of the hull
+// form drop out.  reach < 0: no line is proven.
+template <typename T>
+struct ProofPoint {
+  T kap;
+  float reach;
+  float gy, gq, ny;       // g(d) at step m: gy m^2 - ny; m t^2 / 2 D0: gq m^2
+  float gap, zl, gl, isl; // z to the onset of damage, down to it, g and 1/g' there
+};
+
+// c: the point's centre coefficients (J0, c0); its lines have c2 = c2u and samples at
+// h m, m = 1 .. n_off, tau = h n_off.
+template <typename T>
+__device__ __forceinline__ ProofPoint<T> proof_point(const Point<T>& q, const Line<T>& c, T c2u, int n_off, float tau) {
+  constexpr bool f32 = sizeof(T) == 4;
+  constexpr float nat = f32 ? 0.693147181f : 1.0f, l2e = 1.44269504f;
+  constexpr float eps = f32 ? 1.1920929e-7f : 2.2204460e-16f;      // twice the rounding unit
+  const T lj = lg_t(c.J0);
+  const T kl = fma(q.klk, lj, -q.kmk), kd = fma(q.klk, lj, kl);
+  const T u = fma(lj, kl, c.c0);
+  const T v = fmin(u, q.ub);
+  const float e = float(expk(v)), al = fabsf(float(lj));
+  const float a = float(T(1) - q.A2), b = -nat * float(q.C2);
+  const float be = fmaxf(b * e, 1e-30f), ws = a + be, ibe = __builtin_amdgcn_rcpf(be);
+  const float it = __builtin_amdgcn_rcpf(tau), h = tau * __builtin_amdgcn_rcpf(float(n_off));
+  const float lin = fabsf(float(fma(q.A2, v, -u))), ex = fabsf(float(q.C2)) * e;
+  const float du = 2.0f * fabsf(float(c.c0)) + al * fabsf(float(kl)) + fabsf(float(u)) + (2.5f + 2.0f * al) * fabsf(float(kd));
+  const float noise = nat * eps * (2.0f * (ws * du + 2.0f * ex + lin) + 3.0f * (lin + ex));
+  const float z = -nat * float(u), zb = -nat * float(q.ub), dz = 1e-6f * (fabsf(z) + fabsf(zb));
+  const float klk = float(q.klk), kmk = float(q.kmk), J0 = float(c.J0);
+  const float ratio = klk < 0.0f ? 0.5f * nat * kmk * __builtin_amdgcn_rcpf(klk) : inf_v<float>();   // mu / lambda
+  const float jtop = 0.999f * __builtin_amdgcn_exp2f(l2e + l2e * ratio);
+  ProofPoint<T> r;
+  r.kap = kd * (T(f32 ? 1.4426950408889634 : 1.0) / c.J0);
+  r.gq = -nat * float(c2u) * h * h;
+  r.gy = fminf(ws * r.gq * ibe, 1e30f);
+  r.ny = noise * ibe;
+  r.gap = fmaxf(zb - z - dz, 0.0f);
+  r.zl = fmaxf(z - zb + dz, 0.0f);
+  const float el = __builtin_amdgcn_exp2f(r.zl * l2e);
+  r.gl = el - 1.0f - r.zl + 4e-7f * el;
+  r.isl = __builtin_amdgcn_rcpf(el - 1.0f + 4e-7f * el);
+  if (r.zl > 80.0f) r.zl = inf_v<float>();
+  const bool ok = klk <= 0.0f && kmk < 0.0f && a >= 0.0f && b >= 0.0f && J0 > 0.0f && r.gq > 0.0f && r.gy > r.ny;
+  r.reach = ok ? fminf((jtop - J0) * it, 0.25f * J0 * __builtin_amdgcn_rcpf(h)) : -1.0f;
+  return r;
+}
+
+// The bound over the grid's steps; wave-wide, f wave-uniform.  About 45 issue slots a
+// step and lane: the inverses of g are one step of the fixed points d = 1 + y - e^-d and
+// r = ln(1 + y + r) from s + y/3 and s - y/3, s = sqrt(2 y), each a lower bound (a second
+// step proves 0.1% more lines).
+template <typename T>
+__device__ __forceinline__ LineProof<T> line_proof(const ProofPoint<T>& f, int n_off, float tau) {
+  constexpr float nat = sizeof(T) == 4 ? 0.693147181f : 1.0f, l2e = 1.44269504f, ln2 = 0.693147181f;
+  if (!(f.reach >= 0.0f)) return {f.kap, -1.0f, -1.0f};
+  float p = inf_v<float>();
+  for (int m = 1 + int(threadIdx.x & (kWave - 1)); m <= n_off; m += kWave) {
+    const float mf = float(m), m2 = mf * mf, im = __builtin_amdgcn_rcpf(mf);
+    const float y = fmaf(f.gy, m2, -f.ny), y3 = y * (1.0f / 3.0f);
+    const float s = __builtin_amdgcn_sqrtf(2.0f * y);
+    float d = s + y3, r = s < 3.0f ? s - y3 : 1.5f;
+    d = fmaxf(d, 1.0f + y - __builtin_amdgcn_exp2f(-l2e * d));
+    // the rounding of the steps: 4e-6 relative, 3e-7 absolute
+    const float up = fmaf(d, 1.0f - 4e-6f, fmaf(f.gq * m2, -1.0f - 4e-6f, f.gap - 3e-7f)) * im;
+    p = fminf(p, up);
+    if (f.gap == 0.0f) {                          // wave-uniform
+      r = fmaxf(r, ln2 * __builtin_amdgcn_logf(1.0f + y + r));
+      r = r > f.zl ? fmaf(y - f.gl, f.isl, f.zl) : r;
+      p = fminf(p, fmaf(r, 1.0f - 4e-6f, fmaf(f.gq, m2, -3e-7f)) * im);
+    }
+  }
+  // p was of one step: per unit of t
+  p = seg_min<kWave>(p) * float(n_off) * __builtin_amdgcn_rcpf(tau);
+  return {f.kap, p > 0.0f ? 0.9995f / nat * p : -1.0f, f.reach};
+}
+
+// The directions base + (set bits of mask), all proven: lines whose hull at the centre
+// is the centre value wcs.
+template <typename T>
+__device__ __forceinline__ Env<T> proven_env(T wcs, int base, unsigned long long mask) {
+  return {wcs, base + __ffsll(mask) - 1, 0, 0, 0, (mask & (mask - 1)) ? wcs : inf_v<T>()};
+}
+
+// W at a point in the hull form (the damage energies; see Point), from the lines' part
+// at t = 0 (J0, c0): the value of a line whose hull at the centre is the centre.
+template <typename T, int M>
+__device__ __forceinline__ T centre_value(const Point<T>& q, const Line<T>& c) {
+  if constexpr (M == kFamSTVK) return ws_sample_stvk<T>(T(0), c, q);
+  return ws_sample<T>(T(0), c, q);
+}
+
+// One lamination level at a point (wave-uniform): min over n directions of the line
+// hulls at the centre.  wc = W at the point; line_fn(dir) returns the coefficients of
+// W along direction dir.  order (optional, n entries): the directions, in the order in
+// which they are visited (else 0 .. n - 1); ties in the minimum go to the smaller
+// direction index whatever the visiting order.  warm (optional, 2 n_warm entries owned
+// by this wave) carries each direction's bridge slope at the last call (warm[dir]) and
+// at the call before (warm[n_warm + dir]) to the next, whose bridge search starts from
+// their linear extrapolation (from the last slope alone when the one before is absent):
+// NaN for none; callers whose successive points are close and evenly spaced pass it.
+// c2u: when every line has the same c2 (and, being lines through one point, the same
+// c0), that c2; the polynomial part c0 + c2 t^2 is then formed once per point (NaN: not
+// uniform).  centre (optional): the coefficients of the lines at t = 0 (J0, c0; the rest
+// unused), when the caller has them at hand; else line_fn(0) is taken.  from, step
+// (multiples of the lines a wave takes at once): the wave takes the directions from,
+// from + step, .. only (several waves may share a point).  seed: the result of
+// directions dealt with before, which the others are merged into.  Every lane of the
+// wave must call it.  The result's values are in the hull form; envelope_finish maps
+// them back.
 template <typename T, int S, int K, int M = kFamNH, typename LineFn>
-__device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay,
-                                LineFn line_fn, T* warm = nullptr, T c2u = T(__builtin_nan("")),
-                                int* order = nullptr, const Line<T>* centre = nullptr, int from = 0,
-                                int step = kWave / S) {
+__device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, S, K>& lay, LineFn line_fn,
+                                T* warm = nullptr, int n_warm = 0, T c2u = T(__builtin_nan("")),
+                                const int* order = nullptr, const Line<T>* centre = nullptr, int from = 0,
+                                int step = kWave / S, const Env<T>& seed = env_none<T>()) {
   constexpr int H = K / 2;
   const int lane = threadIdx.x & (kWave - 1);
   const int seg = lane / S;
@@ -909,43 +1038,21 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n_dir, const Layout
   T base[H];
   if (scaled) {
     const Line<T> L0 = centre ? *centre : line_fn(0);
-    if constexpr (M == kFamSTVK) {
-      wcs = ws_sample_stvk<T>(T(0), L0, q);
-    } else {
-      wcs = ws_sample<T>(T(0), L0, q);
-      if (shared) {
+    wcs = centre_value<T, M>(q, L0);
+    if (shared) {
 #pragma unroll
-        for (int h = 0; h < H; ++h) base[h] = fma(c2u, lay.t[h] * lay.t[h], L0.c0);
-      }
+      for (int h = 0; h < H; ++h) base[h] = fma(c2u, lay.t[h] * lay.t[h], L0.c0);
     }
   }
   T wci[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) wci[h] = wcs * lay.inv_m[h];
   const T isc = scaled ? T(1) / q.sc : T(1);
-  if (order) {
-    // stable partition of the directions: warm (bridged last time) first
-    int n_warm = 0;
-    for (int c0 = 0; c0 < n_dir; c0 += kWave)
-      n_warm += __popcll(__ballot(c0 + lane < n_dir && warm[c0 + lane] == warm[c0 + lane]));
-    int seen_warm = 0, seen_cold = 0;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int c0 = 0; c0 < n_dir; c0 += kWave) {
-      const int i = c0 + lane;
-      const bool valid = i < n_dir;
-      const bool hot = valid && warm[i] == warm[i];
-      const unsigned long long mh = __ballot(hot), mc = __ballot(valid && !hot);
-      if (valid)
-        order[hot ? seen_warm + __popcll(mh & below) : n_warm + seen_cold + __popcll(mc & below)] = i;
-      seen_warm += __popcll(mh);
-      seen_cold += __popcll(mc);
-    }
-  }
-  Env<T> best = {inf_v<T>(), 0, 0, 0, 0, inf_v<T>()};
-  for (int m0 = from; m0 < n_dir; m0 += step) {
-    lines_from(line_fn, m0, 0);
-    const bool act = m0 + seg < n_dir;
-    const int dir = order ? order[act ? m0 + seg : n_dir - 1] : (act ? m0 + seg : n_dir - 1);
+  Env<T> best = seg == 0 ? seed : env_none<T>();
+  for (int m0 = from; m0 < n; m0 += step) {
+    const bool act = m0 + seg < n;
+    const int at = act ? m0 + seg : n - 1;
+    const int dir = order ? order[at] : at;
     Line<T> L = line_fn(dir);
     T w[K];
     if constexpr (M == kFamSTVK) {
@@ -992,14 +1099,14 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n_dir, const Layout
     T sg = T(__builtin_nan("")), s1 = sg;
     if (warm && act) {
       s1 = warm[dir];
-      const T s2 = warm[n_dir + dir];
+      const T s2 = warm[n_warm + dir];
       // start from the slope extrapolated linearly from the last two points
       sg = s2 == s2 ? fma(T(2), s1, -s2) : s1;
     }
     const bool hot = warm && __all(act && s1 == s1);
     LineHull<T> lh = hull_centre<T, S, K>(w, wcs, wci, lay, sg, hot, thr);
     if (warm && act && (lane & (S - 1)) == 0) {
-      warm[n_dir + dir] = sg == sg ? s1 : sg;
+      warm[n_warm + dir] = sg == sg ? s1 : sg;
       warm[dir] = sg;
     }
     if (act) {
@@ -1015,19 +1122,14 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n_dir, const Layout
   // across segments: lexicographic (value, direction)
 #pragma unroll
   for (int off = S; off < kWave; off <<= 1) {
-    T oh = __shfl_xor(best.h, off, kWave);
-    int od = __shfl_xor(best.dir, off, kWave);
-    int op = __shfl_xor(best.mp, off, kWave);
-    int oq = __shfl_xor(best.mq, off, kWave);
-    int oc = __shfl_xor(best.capped, off, kWave);
-    T os = __shfl_xor(best.second, off, kWave);
-    bool take = oh < best.h || (oh == best.h && od < best.dir);
-    best.second = take ? fmin(os, best.h) : fmin(best.second, oh);
-    best.h = take ? oh : best.h;
-    best.dir = take ? od : best.dir;
-    best.mp = take ? op : best.mp;
-    best.mq = take ? oq : best.mq;
-    best.capped |= oc;
+    Env<T> o;
+    o.h = __shfl_xor(best.h, off, kWave);
+    o.dir = __shfl_xor(best.dir, off, kWave);
+    o.mp = __shfl_xor(best.mp, off, kWave);
+    o.mq = __shfl_xor(best.mq, off, kWave);
+    o.capped = __shfl_xor(best.capped, off, kWave);
+    o.second = __shfl_xor(best.second, off, kWave);
+    env_merge(best, o);
   }
   return best;
 }
@@ -1045,12 +1147,62 @@ __device__ __forceinline__ Env<T> envelope_finish(const Point<T>& q, T wc, Env<T
 
 // One lamination level at a point by one wave, all directions.
 template <typename T, int S, int K, int M = kFamNH, typename LineFn>
-__device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay,
-                                 LineFn line_fn, T* warm = nullptr, T c2u = T(__builtin_nan("")),
-                                 int* order = nullptr, const Line<T>* centre = nullptr) {
-  return envelope_finish<T, M>(q, wc, envelope_scan<T, S, K, M>(q, wc, n_dir, lay, line_fn, warm, c2u, order, centre));
+__device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay, LineFn line_fn,
+                                 T c2u = T(__builtin_nan("")), const Line<T>* centre = nullptr) {
+  return envelope_finish<T, M>(
+      q, wc, envelope_scan<T, S, K, M>(q, wc, n_dir, lay, line_fn, nullptr, 0, c2u, nullptr, centre));
 }
 
+// The same at one of successive points (see warm of envelope_scan; 2 n_dir entries),
+// with the lines' part at t = 0 (centre).  order (n_dir entries owned by this wave):
+// the directions are visited with those that had a bridge last time first, so that
+// lines needing a bridge search share wavefronts, and without those that need no
+// sampling (line_proof, for tau the grid's half width), whose slope is forgotten as a
+// search that finds no bridge forgets it.
+template <typename T, int S, int K, int M = kFamNH, typename LineFn>
+__device__ Env<T> envelope_next(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay, LineFn line_fn,
+                                T* warm, int* order, const Line<T>& centre, float tau,
+                                T c2u = T(__builtin_nan(""))) {
+  const int lane = threadIdx.x & (kWave - 1);
+  Env<T> seed = env_none<T>();
+  const bool prove = M == kFamNH && q.model == 0 && c2u == c2u && n_dir > kWave / S;
+  T wcs = T(0);
+  LineProof<T> pf{};
+  if (prove) {
+    wcs = centre_value<T, M>(q, centre);
+    pf = line_proof<T>(proof_point<T>(q, centre, c2u, lay.c, tau), lay.c, tau);
+  }
+  // a stable partition of the unproven directions: bridged last time, then the others
+  unsigned skip = 0;                 // this lane's proven directions, bit c0 / 64 (n_dir <= 32 waves)
+  int n_hot = 0;
+  for (int c0 = 0; c0 < n_dir; c0 += kWave) {
+    const int i = c0 + lane;
+    const bool valid = i < n_dir;
+    if (prove) {
+      const bool proven = valid && pf(line_fn(valid ? i : 0));
+      const unsigned long long mp = __ballot(proven);
+      if (mp) env_merge(seed, proven_env(wcs, c0, mp));
+      if (proven) {
+        warm[i] = warm[n_dir + i] = T(__builtin_nan(""));
+        skip |= 1u << (c0 / kWave);
+      }
+    }
+    n_hot += __popcll(__ballot(valid && warm[i] == warm[i]));
+  }
+  int seen_hot = 0, seen_cold = 0;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  for (int c0 = 0; c0 < n_dir; c0 += kWave) {
+    const int i = c0 + lane;
+    const bool valid = i < n_dir && !((skip >> (c0 / kWave)) & 1u);
+    const bool hot = valid && warm[i] == warm[i];
+    const unsigned long long mh = __ballot(hot), mc = __ballot(valid && !hot);
+    if (valid) order[hot ? seen_hot + __popcll(mh & below) : n_hot + seen_cold + __popcll(mc & below)] = i;
+    seen_hot += __popcll(mh);
+    seen_cold += __popcll(mc);
+  }
+  return envelope_finish<T, M>(q, wc, envelope_scan<T, S, K, M>(q, wc, n_hot + seen_cold, lay, line_fn, warm, n_dir,
+                                                                c2u, order, &centre, 0, kWave / S, seed));
+}
 
 // Line coefficients of one wave's directions in LDS: what differs between the lines
 // through a point (J1, c1, c2, or c1 .. c4 for St. Venant-Kirchhoff).
@@ -1095,7 +1247,7 @@ __device__ Env<T> envelope_geom(const Point<T>& q, const typename GeomOf<D, M>::
 #pragma unroll
     for (int i = 0; i < D; ++i) { a[i] = lv.a[dd * D + i]; b[i] = lv.b[dd * D + i]; }
     return line_of<T, D, M>(q, g, a, b);
-  }, nullptr, T(q.kq * lv.ab2), nullptr, (M != kFamSTVK && q.model == 0) ? &c : nullptr);
+  }, T(q.kq * lv.ab2), (M != kFamSTVK && q.model == 0) ? &c : nullptr);
 }
 
 // The same at point G.

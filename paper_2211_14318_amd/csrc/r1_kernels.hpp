@@ -183,26 +183,6 @@ __device__ __forceinline__ Line<T> level_line(const PointSetup<T, D, M>& s, cons
   return line_of<T, D, M>(s.q, s.g, a, b);
 }
 
-// The lines of a point from its wave's table: entries base .. hold the directions
-// from first on, up to the end of the level or the table (step = 0: the caller has
-// filled in the whole level; else every step directions the table is refilled).
-template <typename T, int D, int M>
-struct TableLines {
-  const PointSetup<T, D, M>& s;
-  const Level& lv;
-  LineTable<T, M>& tab;
-  Line<T> c;                   // J0, c0
-  int base, first, step;
-  __device__ __forceinline__ Line<T> operator()(int dir) const { return tab.get(base + dir - first, c); }
-  __device__ __forceinline__ void fill(int m0) {
-    if (step == 0 || m0 % step != 0) return;     // wave-uniform
-    first = m0;
-    wave_lds_fence();                            // reads of the entries before are done
-    for (int m = lane_id(); m < step && m0 + m < lv.n_dir; m += kWave) tab.put(m, level_line<T, D, M>(s, lv, m0 + m));
-    wave_lds_fence();
-  }
-};
-
 // One-level launch: a block of 4 waves takes a.pts_per_wave (<= kPointsPerWave)
 // points per wave.  Their constants are formed by one thread per point into LDS
 // first (a point's FP64 set-up then costs a lane, not a wavefront), then the
@@ -233,16 +213,28 @@ template <typename T, int D, int S, int K, int M>
 __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KArgs a) {
   __shared__ PointSetup<T, D, M> ps[kPointsPerBlock];
   __shared__ LineTable<T, M> tabs[4];
+  __shared__ int orders[4][M == kFamSTVK ? 1 : kTabLines];
+  __shared__ ProofPoint<T> proofs[M == kFamSTVK ? 1 : kPointsPerBlock];
   const int per_block = 4 * a.pts_per_wave;
   const int64_t p0 = int64_t(blockIdx.x) * per_block;
-  if (int(threadIdx.x) < per_block && p0 + threadIdx.x < a.n) ps[threadIdx.x] = point_setup<T, D, M>(a, p0 + threadIdx.x);
+  const int n_dir = a.lv0.n_dir, n_off = (a.lv0.n_t - 1) / 2;
+  // lines shown to have a vertex at the centre are not sampled (line_proof), where that
+  // can save a wave step
+  const bool prove = M == kFamNH && a.mat.model == 0 && a.lv0.ab2 == a.lv0.ab2 && n_dir > kWave / S;
+  if (int(threadIdx.x) < per_block && p0 + threadIdx.x < a.n) {
+    const PointSetup<T, D, M> s = point_setup<T, D, M>(a, p0 + threadIdx.x);
+    ps[threadIdx.x] = s;
+    if constexpr (M == kFamNH)
+      if (prove)
+        proofs[threadIdx.x] = proof_point<T>(s.q, level_line<T, D, M>(s, a.lv0, 0), T(s.q.kq * a.lv0.ab2), n_off,
+                                             float(a.lv0.tau));
+  }
   __syncthreads();
   const Layout<T, S, K> lay = make_layout<T, S, K>(a.lv0);
   const int wave = threadIdx.x / kWave;
   LineTable<T, M>& tab = tabs[wave];
   // few directions: the lines of all of the wave's points at once; else a point's,
   // kTabLines at a time
-  const int n_dir = a.lv0.n_dir;
   const bool whole = n_dir * a.pts_per_wave <= kTabLines;
   if (whole) {
     for (int e = lane_id(); e < n_dir * a.pts_per_wave; e += kWave) {
@@ -260,10 +252,44 @@ __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KA
       if (lane_id() == 0) write_bad_point<T, D>(a, p, s.state == 1, a.want_stress);
       continue;
     }
-    TableLines<T, D, M> lines{s, a.lv0, tab, level_line<T, D, M>(s, a.lv0, 0), whole ? i * n_dir : 0, 0,
-                              whole ? 0 : kTabLines};
-    const Env<T> e = envelope_lines<T, S, K, M>(s.q, s.wc, n_dir, lay, lines, nullptr, T(s.q.kq * a.lv0.ab2), nullptr,
-                                                &lines.c);
+    const Line<T> c = level_line<T, D, M>(s, a.lv0, 0);       // J0, c0
+    const T c2u = T(s.q.kq * a.lv0.ab2);
+    LineProof<T> pf{};
+    T wcs = T(0);
+    if (prove) {
+      pf = line_proof<T>(proofs[slot], n_off, float(a.lv0.tau));
+      wcs = centre_value<T, M>(s.q, c);
+    }
+    Env<T> e = env_none<T>();
+    for (int m0 = 0; m0 < n_dir; m0 += kTabLines) {
+      const int n = min(n_dir - m0, kTabLines);
+      if (!whole) {
+        wave_lds_fence();                      // reads of the entries before are done
+        for (int m = lane_id(); m < n; m += kWave) tab.put(m, level_line<T, D, M>(s, a.lv0, m0 + m));
+        wave_lds_fence();
+      }
+      const int off = whole ? i * n_dir : -m0;
+      const auto lines = [&](int dir) { return tab.get(dir + off, c); };
+      if constexpr (M == kFamSTVK) {
+        e = envelope_scan<T, S, K, M>(s.q, s.wc, m0 + n, lay, lines, nullptr, 0, c2u, nullptr, &c, m0, kWave / S, e);
+      } else {
+        int* order = orders[wave];
+        int count = 0;
+        wave_lds_fence();
+        for (int c0 = m0; c0 < m0 + n; c0 += kWave) {
+          const int dir = c0 + lane_id();
+          const bool valid = dir < m0 + n;
+          const bool proven = prove && valid && pf(lines(valid ? dir : m0));
+          const unsigned long long mp = __ballot(proven), mo = __ballot(valid && !proven);
+          if (mp) env_merge(e, proven_env(wcs, c0, mp));
+          if (valid && !proven) order[count + __popcll(mo & ((1ull << lane_id()) - 1ull))] = dir;
+          count += __popcll(mo);
+        }
+        wave_lds_fence();
+        e = envelope_scan<T, S, K, M>(s.q, s.wc, count, lay, lines, nullptr, 0, c2u, order, &c, 0, kWave / S, e);
+      }
+    }
+    e = envelope_finish<T, M>(s.q, s.wc, e);
     if (lane_id() == 0) write_depth1<T, D, M, true>(a, p, a.lv0, s.q, s.g.G, s.bn, e);
   }
 }
@@ -292,20 +318,12 @@ __global__ __launch_bounds__(kWave * kSplitWaves) void k_depth1_split(KArgs a) {
   const Layout<T, S, K> lay = make_layout<T, S, K>(lv);
   const Line<T> c = level_line<T, D, M>(s, lv, 0);
   Env<T> e = envelope_scan<T, S, K, M>(s.q, s.wc, lv.n_dir, lay, [&](int dd) { return level_line<T, D, M>(s, lv, dd); },
-                                       nullptr, T(s.q.kq * lv.ab2), nullptr, &c, wave * NSEG, waves * NSEG);
+                                       nullptr, 0, T(s.q.kq * lv.ab2), nullptr, &c, wave * NSEG, waves * NSEG);
   if (lane_id() == 0) part[wave] = e;
   __syncthreads();
   if (wave != 0) return;
   e = part[0];
-  for (int w = 1; w < waves; ++w) {
-    const Env<T> o = part[w];
-    const bool take = o.h < e.h || (o.h == e.h && o.dir < e.dir);
-    const T second = take ? fmin(o.second, e.h) : fmin(e.second, o.h);
-    const int capped = e.capped | o.capped;
-    if (take) e = o;
-    e.second = second;
-    e.capped = capped;
-  }
+  for (int w = 1; w < waves; ++w) env_merge(e, part[w]);
   e = envelope_finish<T, M>(s.q, s.wc, e);
   if (threadIdx.x == 0) write_depth1<T, D, M, false>(a, p, lv, s.q, s.g.G, s.bn, e);
 }
@@ -558,7 +576,7 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
         v = wc;
         if (wc < inf_v<T>()) {
           const T tt = T(t);
-          Env<T> e = envelope_lines<T, S, K, M>(q, wc, li.n_dir, lay, [&](int dd) {
+          Env<T> e = envelope_next<T, S, K, M>(q, wc, li.n_dir, lay, [&](int dd) {
             const T* cf = coef + NC * dd;
             Line<T> L;
             L.J0 = T(0);
@@ -569,7 +587,7 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
             L.c3 = fma(tt, cf[8], cf[7]);
             L.c4 = cf[9];
             return L;
-          }, warm_w, T(__builtin_nan("")), order_w);
+          }, warm_w, order_w, L0, float(li.tau));
           v = e.h;
           capped |= e.capped;
         }
@@ -597,10 +615,10 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
         v = wc;
         if (wc < inf_v<T>()) {
           const T tt = T(t);
-          Env<T> e = envelope_lines<T, S, K>(q, wc, li.n_dir, lay, [&](int dd) {
+          Env<T> e = envelope_next<T, S, K>(q, wc, li.n_dir, lay, [&](int dd) {
             const T* cf = coef + NC * dd;
             return Line<T>{L0.J0, T(fma(tt, cf[1], cf[0])), L0.c0, T(fma(tt, cf[3], cf[2])), cf[4]};
-          }, warm_w, T(q.kq * li.ab2), order_w);
+          }, warm_w, order_w, L0, float(li.tau), T(q.kq * li.ab2));
           v = e.h;
           capped |= e.capped;
         }

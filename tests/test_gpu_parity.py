@@ -281,3 +281,49 @@ def test_few_and_many_points_give_the_same_bits(lib, kind, dim, model, dirs, nt)
     ok[[3, 5]] = False
     _, _, W, _, _ = run_oracle(cfg, few["F_in"][:, ok].copy(), few["bn_in"][ok].copy(), model, want_tree=False)
     assert PA.energy_errors(few["W"][ok], W, kind).max() <= PA.RTOL[kind]
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,dirs,nt,tau,mat,sigma,beta_max,scale", [
+    (2, (4, 4), 201, 1.0, {}, 0.3, 0.5, 1.0),                                     # 4 lines at once, as the workload
+    (2, (9, 8), 1025, 0.5, {}, 0.3, 0.2, 1.0),                                    # steps of 1e-3: rounding at its largest
+    (2, (5, 4), 257, 1.5, dict(D_inf=0.9, D0=0.3, lam=0.5), 0.5, 0.0, 1.0),       # virgin points
+    (2, (5, 4), 257, 1.5, dict(D_inf=0.5, D0=2.0, lam=40.0), 0.2, 0.1, 1.0),      # ln J soon beyond 1 + mu / lambda
+    (2, (7, 7), 65, 1.0, dict(D_inf=0.999, D0=0.02, mu=5.0), 0.4, 3.0, 1.0),      # heavy damage, high thresholds
+    (2, (7, 7), 65, 1.0, dict(lam=0.0), 0.3, 0.5, 1.0),                           # no volumetric part
+    (2, (5, 5), 129, 1.0, {}, 0.3, 0.5, 1.7),                                     # |a| = 1.7 for every line
+    (2, (5, 5), 129, 1.0, {}, 0.3, 0.5, None),                                    # lines of different |a|
+    (2, (2, 2), 129, 1.0, {}, 0.3, 0.5, 1.0),                                     # fewer lines than a wave takes
+    (3, (18, 17), 33, 1.0, {}, 0.2, 0.5, 1.0),                                    # a refilled table
+    (3, (8, 8), 257, 0.8, dict(D_inf=0.6, D0=0.5), 0.4, 0.05, 1.0),
+])
+def test_lines_left_unsampled_change_nothing(lib, kind, dim, dirs, nt, tau, mat, sigma, beta_max, scale):
+    """Large batches leave out the lines whose centre is shown to be a hull vertex without
+    sampling; small ones sample every line: the same values, trees and flags, bit for bit.
+    Points from the rest state to large strains, some with det F near zero."""
+    cfg = WL.small_random(dim, 512, dirs, nt, tau=tau, sigma=sigma, det_min=1e-3, beta_max=beta_max, seed_tag=940 + dim)
+    cfg["material"].update(mat)
+    a = cfg["levels"][0]["a"]
+    a *= np.linspace(0.5, 2.0, len(a))[:, None] if scale is None else scale
+    F = cfg["F"]
+    F[:, :64] = np.eye(dim).reshape(-1, 1) + 1e-3 * (F[:, :64] - np.eye(dim).reshape(-1, 1))
+    F[:, 64:128] *= 1.5
+    few = run_gpu(lib, cfg, kind)
+    many = run_gpu(lib, dict(cfg, F=np.tile(F, (1, 17)), beta_n=np.tile(cfg["beta_n"], 17)), kind)
+    for k in ("W", "P", "flags", "tree"):
+        c = many[k][:, -512:] if k == "P" else many[k][-512:]
+        assert np.array_equal(few[k], c, equal_nan=k in ("W", "P")), (k, int((few[k] != c).sum()))
+    assert np.isfinite(few["W"]).all()
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("mat,beta_max", [({}, 0.5), (dict(D_inf=0.9, D0=0.3, lam=0.5), 0.0),
+                                          (dict(D_inf=0.5, D0=2.0, lam=40.0), 0.1)])
+def test_lines_left_unsampled_in_two_levels(lib, kind, mat, beta_max):
+    """The same inside outer lines, against the oracle's energies."""
+    cfg = WL.small_random(2, 24, (4, 4), 33, tau=1.2, depth=2, inner=(5, 4, 65), sigma=0.3, beta_max=beta_max,
+                          seed_tag=950)
+    cfg["material"].update(mat)
+    g = run_gpu(lib, cfg, kind)
+    _, _, W, _, _ = run_oracle(cfg, g["F_in"], g["bn_in"], want_tree=False)
+    assert PA.energy_errors(g["W"], W, kind).max() <= PA.RTOL[kind]
