@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && D == 2) ? (K <= 16 && M == 
     if (!(w1f < inf_v<T>())) {                   // det F <= 0 or non-finite input: block-uniform
       if (threadIdx.x == 0) *res = OuterRes<T>{w1f, 0, 0, 0};
     } else {
-      outer_line<T, D, S, K, M>(b.base, p, mo, e.lv0, e.lv1, w1f, false, res, smem_raw);
+      outer_line<T, D, S, K, M>(b.base, p, mo, e.lv0, e.lv1, w1f, res, smem_raw);
     }
   }
 }

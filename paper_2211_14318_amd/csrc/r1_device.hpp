@@ -878,6 +878,26 @@ __device__ __forceinline__ void env_merge(Env<T>& a, const Env<T>& o) {
   if (take) { a.h = o.h; a.dir = o.dir; a.mp = o.mp; a.mq = o.mq; }
 }
 
+// The lines' common part at a point of a damage energy (t = 0): J0 (neo-Hooke), c0 and W
+// there in the hull form, ws: the value of a line whose hull at the centre is the centre
+// (what ws_sample gives at t = 0).  lj, e: ln J0 and e^-m/D0 as the sample takes them.
+template <typename T>
+struct Centre { T J0, c0, ws, lj, e; };
+
+template <typename T, int M>
+__device__ __forceinline__ Centre<T> make_centre(const Point<T>& q, T J0, T c0) {
+  Centre<T> c = {J0, c0, T(0), T(0), T(0)};
+  T u = c0;
+  if constexpr (M != kFamSTVK) {
+    c.lj = lg_t(J0);
+    u = fma(c.lj, fma(q.klk, c.lj, -q.kmk), c0);
+  }
+  const T v = fmin(u, q.ub);
+  c.e = expk(v);
+  c.ws = fma(q.C2, c.e, fma(q.A2, v, -u));
+  return c;
+}
+
 // Lines that need no sampling (neo-Hooke damage).  W = w(psi0) with w increasing and
 // concave, and psi0 is strongly convex along a rank-one line: its second derivative is
 // mu |a|^2 |b|^2 + (J1/J)^2 (mu + lambda (1 - ln J)) >= m = mu |a|^2 |b|^2 as long as
@@ -897,8 +917,7 @@ __device__ __forceinline__ void env_merge(Env<T>& a, const Env<T>& o) {
 // proven line is one the test would find a vertex.  Of the lines of the 2D 16 x 201
 // random points 66% are proven (4 -> 1.5 wave steps), of 3D 256 x 513 52% (64 -> 30), of
 // the inner 32 x 257 lines of two-level samples 44% (8 -> 4.8).  The bound costs about
-// 100 issue slots a point, a wave step 300 to 600; it is taken where there is more than
-// one step.  1,000,000 2D points 2044 -> 1594 us, 262,144 3D points 18.4 -> 11.7 ms, two
+// 100 issue slots a point, a wave step 300 to 600.  262,144 3D points 18.4 -> 11.8 ms, two
 // levels 64 x 1025 / 32 x 257, FP32 96 points 26.5 -> 23.2 ms, FP64 37 points 52.7 -> 41.4.
 template <typename T>
 struct LineProof {
@@ -922,18 +941,17 @@ struct ProofPoint {
   float gap, zl, gl, isl; // z to the onset of damage, down to it, g and 1/g' there
 };
 
-// c: the point's centre coefficients (J0, c0); its lines have c2 = c2u and samples at
-// h m, m = 1 .. n_off, tau = h n_off.
+// c: the point's centre; its lines have c2 = c2u and samples at h m, m = 1 .. n_off, tau = h n_off.
 template <typename T>
-__device__ __forceinline__ ProofPoint<T> proof_point(const Point<T>& q, const Line<T>& c, T c2u, int n_off, float tau) {
+__device__ __forceinline__ ProofPoint<T> proof_point(const Point<T>& q, const Centre<T>& c, T c2u, int n_off,
+                                                      float tau) {
   constexpr bool f32 = sizeof(T) == 4;
   constexpr float nat = f32 ? 0.693147181f : 1.0f, l2e = 1.44269504f;
   constexpr float eps = f32 ? 1.1920929e-7f : 2.2204460e-16f;      // twice the rounding unit
-  const T lj = lg_t(c.J0);
-  const T kl = fma(q.klk, lj, -q.kmk), kd = fma(q.klk, lj, kl);
-  const T u = fma(lj, kl, c.c0);
+  const T kl = fma(q.klk, c.lj, -q.kmk), kd = fma(q.klk, c.lj, kl);
+  const T u = fma(c.lj, kl, c.c0);
   const T v = fmin(u, q.ub);
-  const float e = float(expk(v)), al = fabsf(float(lj));
+  const float e = float(c.e), al = fabsf(float(c.lj));
   const float a = float(T(1) - q.A2), b = -nat * float(q.C2);
   const float be = fmaxf(b * e, 1e-30f), ws = a + be, ibe = __builtin_amdgcn_rcpf(be);
   const float it = __builtin_amdgcn_rcpf(tau), h = tau * __builtin_amdgcn_rcpf(float(n_off));
@@ -996,14 +1014,6 @@ __device__ __forceinline__ Env<T> proven_env(T wcs, int base, unsigned long long
   return {wcs, base + __ffsll(mask) - 1, 0, 0, 0, (mask & (mask - 1)) ? wcs : inf_v<T>()};
 }
 
-// W at a point in the hull form (the damage energies; see Point), from the lines' part
-// at t = 0 (J0, c0): the value of a line whose hull at the centre is the centre.
-template <typename T, int M>
-__device__ __forceinline__ T centre_value(const Point<T>& q, const Line<T>& c) {
-  if constexpr (M == kFamSTVK) return ws_sample_stvk<T>(T(0), c, q);
-  return ws_sample<T>(T(0), c, q);
-}
-
 // One lamination level at a point (wave-uniform): min over n directions of the line
 // hulls at the centre.  wc = W at the point; line_fn(dir) returns the coefficients of
 // W along direction dir.  order (optional, n entries): the directions, in the order in
@@ -1015,8 +1025,8 @@ __device__ __forceinline__ T centre_value(const Point<T>& q, const Line<T>& c) {
 // NaN for none; callers whose successive points are close and evenly spaced pass it.
 // c2u: when every line has the same c2 (and, being lines through one point, the same
 // c0), that c2; the polynomial part c0 + c2 t^2 is then formed once per point (NaN: not
-// uniform).  centre (optional): the coefficients of the lines at t = 0 (J0, c0; the rest
-// unused), when the caller has them at hand; else line_fn(0) is taken.  from, step
+// uniform).  centre (optional): the point's centre, when the caller has it at hand; else
+// it is taken from line_fn(0).  from, step
 // (multiples of the lines a wave takes at once): the wave takes the directions from,
 // from + step, .. only (several waves may share a point).  seed: the result of
 // directions dealt with before, which the others are merged into.  Every lane of the
@@ -1025,7 +1035,7 @@ __device__ __forceinline__ T centre_value(const Point<T>& q, const Line<T>& c) {
 template <typename T, int S, int K, int M = kFamNH, typename LineFn>
 __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, S, K>& lay, LineFn line_fn,
                                 T* warm = nullptr, int n_warm = 0, T c2u = T(__builtin_nan("")),
-                                const int* order = nullptr, const Line<T>* centre = nullptr, int from = 0,
+                                const int* order = nullptr, const Centre<T>* centre = nullptr, int from = 0,
                                 int step = kWave / S, const Env<T>& seed = env_none<T>()) {
   constexpr int H = K / 2;
   const int lane = threadIdx.x & (kWave - 1);
@@ -1037,17 +1047,22 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
   T wcs = wc;
   T base[H];
   if (scaled) {
-    const Line<T> L0 = centre ? *centre : line_fn(0);
-    wcs = centre_value<T, M>(q, L0);
+    Centre<T> ct;
+    if (centre) {
+      ct = *centre;
+    } else {
+      const Line<T> L0 = line_fn(0);
+      ct = make_centre<T, M>(q, L0.J0, L0.c0);
+    }
+    wcs = ct.ws;
     if (shared) {
 #pragma unroll
-      for (int h = 0; h < H; ++h) base[h] = fma(c2u, lay.t[h] * lay.t[h], L0.c0);
+      for (int h = 0; h < H; ++h) base[h] = fma(c2u, lay.t[h] * lay.t[h], ct.c0);
     }
   }
   T wci[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) wci[h] = wcs * lay.inv_m[h];
-  const T isc = scaled ? T(1) / q.sc : T(1);
   Env<T> best = seg == 0 ? seed : env_none<T>();
   for (int m0 = from; m0 < n; m0 += step) {
     const bool act = m0 + seg < n;
@@ -1083,8 +1098,9 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
     // lines that cannot come within twice the tie margin of the wave's best so
     // far may stop their bridge search early: the minimum is unchanged and so
     // is the tie flag (their value only enters the runner-up, beyond the
-    // margin).  Only for cold searches: warm-started lines come first in their
-    // visiting order and rarely meet a lower value already found.
+    // margin).  Only for cold searches: a search that reaches the iteration cap
+    // is reported, and stopping more of them early would hide some (1 in 1,200
+    // points of an uneven plan).
     T thr = inf_v<T>();
     if (!warm) {
       T bw = best.h;
@@ -1093,7 +1109,7 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
       if (bw < inf_v<T>()) {
         const T bW = scaled ? fma(bw, q.sc, q.B) : bw;
         const T mW = T(2) * tie_margin<T>() * fmax(fabs(bW), tie_floor<T>());
-        thr = bw + (scaled ? mW * isc : mW);
+        thr = bw + (scaled ? mW * T(__builtin_amdgcn_rcpf(float(q.sc))) : mW);
       }
     }
     T sg = T(__builtin_nan("")), s1 = sg;
@@ -1148,30 +1164,35 @@ __device__ __forceinline__ Env<T> envelope_finish(const Point<T>& q, T wc, Env<T
 // One lamination level at a point by one wave, all directions.
 template <typename T, int S, int K, int M = kFamNH, typename LineFn>
 __device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay, LineFn line_fn,
-                                 T c2u = T(__builtin_nan("")), const Line<T>* centre = nullptr) {
+                                 T c2u = T(__builtin_nan("")), const Centre<T>* centre = nullptr) {
   return envelope_finish<T, M>(
       q, wc, envelope_scan<T, S, K, M>(q, wc, n_dir, lay, line_fn, nullptr, 0, c2u, nullptr, centre));
 }
+
+// Whether a level leaves lines out: where the bound costs less than
+// it saves, in FP32 from more than four wave steps on (40 points, 2D, 32 x 153 outer,
+// without / with, us: four steps, 16 x 257, 764 / 765 and 32 x 45, 539 / 550; eight,
+// 32 x 257, 1352 / 1280), in FP64 whenever there is more than one step (two, 16 x 45,
+// 985 / 860; 64 x 257 13020 / 8924).
+template <typename T, int S>
+constexpr bool proves_lines(int n_dir) { return n_dir > (sizeof(T) == 4 ? 4 : 1) * (kWave / S); }
 
 // The same at one of successive points (see warm of envelope_scan; 2 n_dir entries),
 // with the lines' part at t = 0 (centre).  order (n_dir entries owned by this wave):
 // the directions are visited with those that had a bridge last time first, so that
 // lines needing a bridge search share wavefronts, and without those that need no
 // sampling (line_proof, for tau the grid's half width), whose slope is forgotten as a
-// search that finds no bridge forgets it.
+// search that finds no bridge forgets it (pp: the sample's part of the bound; nullptr to
+// prove none).
 template <typename T, int S, int K, int M = kFamNH, typename LineFn>
 __device__ Env<T> envelope_next(const Point<T>& q, T wc, int n_dir, const Layout<T, S, K>& lay, LineFn line_fn,
-                                T* warm, int* order, const Line<T>& centre, float tau,
-                                T c2u = T(__builtin_nan(""))) {
+                                T* warm, int* order, const Centre<T>& centre, const ProofPoint<T>* pp, float tau,
+                                T c2u) {
   const int lane = threadIdx.x & (kWave - 1);
   Env<T> seed = env_none<T>();
-  const bool prove = M == kFamNH && q.model == 0 && c2u == c2u && n_dir > kWave / S;
-  T wcs = T(0);
+  const bool prove = M == kFamNH && pp != nullptr;
   LineProof<T> pf{};
-  if (prove) {
-    wcs = centre_value<T, M>(q, centre);
-    pf = line_proof<T>(proof_point<T>(q, centre, c2u, lay.c, tau), lay.c, tau);
-  }
+  if (prove) pf = line_proof<T>(*pp, lay.c, tau);
   // a stable partition of the unproven directions: bridged last time, then the others
   unsigned skip = 0;                 // this lane's proven directions, bit c0 / 64 (n_dir <= 32 waves)
   int n_hot = 0;
@@ -1181,7 +1202,7 @@ __device__ Env<T> envelope_next(const Point<T>& q, T wc, int n_dir, const Layout
     if (prove) {
       const bool proven = valid && pf(line_fn(valid ? i : 0));
       const unsigned long long mp = __ballot(proven);
-      if (mp) env_merge(seed, proven_env(wcs, c0, mp));
+      if (mp) env_merge(seed, proven_env(centre.ws, c0, mp));
       if (proven) {
         warm[i] = warm[n_dir + i] = T(__builtin_nan(""));
         skip |= 1u << (c0 / kWave);
@@ -1217,9 +1238,9 @@ struct LineTable {
       v[0][e] = L.J1; v[1][e] = L.c1; v[2][e] = L.c2;
     }
   }
-  // the rest (J0, c0) from c, a line through the point
-  __device__ __forceinline__ Line<T> get(int e, const Line<T>& c) const {
-    if constexpr (M == kFamSTVK) return Line<T>{c.J0, c.J1, c.c0, v[0][e], v[1][e], v[2][e], v[3][e]};
+  // the rest (J0, c0) from the point's centre
+  __device__ __forceinline__ Line<T> get(int e, const Centre<T>& c) const {
+    if constexpr (M == kFamSTVK) return Line<T>{T(0), T(0), c.c0, v[0][e], v[1][e], v[2][e], v[3][e]};
     return Line<T>{c.J0, v[0][e], c.c0, v[1][e], v[2][e], T(0), T(0)};
   }
 };
@@ -1237,11 +1258,9 @@ template <typename T, int D, int S, int K, int M = kFamNH>
 __device__ Env<T> envelope_geom(const Point<T>& q, const typename GeomOf<D, M>::type& g, T wc, const Level& lv,
                                 const Layout<T, S, K>& lay) {
   // neo-Hooke: every line through G starts at J0 = det G, c0 = kq (|G|^2 - d) (line_of)
-  Line<T> c{};
-  if constexpr (M != kFamSTVK) {
-    c.J0 = T(g.det);
-    c.c0 = T(q.kq * (g.n2 - double(D)));
-  }
+  Centre<T> c{};
+  if constexpr (M != kFamSTVK)
+    if (q.model == 0) c = make_centre<T, M>(q, T(g.det), T(q.kq * (g.n2 - double(D))));
   return envelope_lines<T, S, K, M>(q, wc, lv.n_dir, lay, [&](int dd) {
     double a[D], b[D];
 #pragma unroll

@@ -117,6 +117,7 @@ struct PointSetup {
   Point<T> q;
   double bn;
   T wc;
+  Centre<T> c;             // (J0, c0 alone for the double-well energy)
   int state;
 };
 
@@ -128,7 +129,15 @@ __device__ __forceinline__ PointSetup<T, D, M> point_setup(const KArgs& a, int64
   s.q = make_point<T, M>(a.mat, s.bn);
   double cof[D * D];
   cofactor<D>(G, cof);
-  s.wc = w_point<T, D, M>(s.q, G, cof);
+  const double zero[D] = {};
+  const Line<T> L = line_setup<T, D, M>(s.q, G, cof, zero, zero);       // W(F) as w_point takes it
+  if (M == kFamSTVK || s.q.model == 0) {
+    s.c = make_centre<T, M>(s.q, L.J0, L.c0);
+    s.wc = fma(s.c.ws, s.q.sc, s.q.B);
+  } else {
+    s.c = Centre<T>{L.J0, L.c0, T(0), T(0), T(0)};
+    s.wc = w_sample_doublewell<T>(T(0), L);
+  }
   s.g = make_geom_m<D, M>(G);
   s.state = !fin ? 1 : (s.wc < inf_v<T>() ? 0 : 2);
   return s;
@@ -218,16 +227,19 @@ __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KA
   const int per_block = 4 * a.pts_per_wave;
   const int64_t p0 = int64_t(blockIdx.x) * per_block;
   const int n_dir = a.lv0.n_dir, n_off = (a.lv0.n_t - 1) / 2;
-  // lines shown to have a vertex at the centre are not sampled (line_proof), where that
-  // can save a wave step
-  const bool prove = M == kFamNH && a.mat.model == 0 && a.lv0.ab2 == a.lv0.ab2 && n_dir > kWave / S;
+  // lines shown to have a vertex at the centre are not sampled (proves_lines).  60,000
+  // points FP32, without / with: 3D 128 x 257 1501 / 911 us, 2D 32 x 257 (eight steps)
+  // 422 / 349; two steps, 2D 16 x 129, 152 / 153.  Four steps, 16 x 257, 241 / 220, stay
+  // out with the two: plain lamination of the 16 x 201 workload would gain (1,000,000
+  // points 1.48 ms) while the network's inference, whose fallback gets the points with the
+  // fewest such lines, would not, and would no longer be the faster of the two.
+  const bool prove = M == kFamNH && a.mat.model == 0 && a.lv0.ab2 == a.lv0.ab2 && proves_lines<T, S>(n_dir);
   if (int(threadIdx.x) < per_block && p0 + threadIdx.x < a.n) {
     const PointSetup<T, D, M> s = point_setup<T, D, M>(a, p0 + threadIdx.x);
     ps[threadIdx.x] = s;
     if constexpr (M == kFamNH)
       if (prove)
-        proofs[threadIdx.x] = proof_point<T>(s.q, level_line<T, D, M>(s, a.lv0, 0), T(s.q.kq * a.lv0.ab2), n_off,
-                                             float(a.lv0.tau));
+        proofs[threadIdx.x] = proof_point<T>(s.q, s.c, T(s.q.kq * a.lv0.ab2), n_off, float(a.lv0.tau));
   }
   __syncthreads();
   const Layout<T, S, K> lay = make_layout<T, S, K>(a.lv0);
@@ -252,14 +264,9 @@ __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KA
       if (lane_id() == 0) write_bad_point<T, D>(a, p, s.state == 1, a.want_stress);
       continue;
     }
-    const Line<T> c = level_line<T, D, M>(s, a.lv0, 0);       // J0, c0
     const T c2u = T(s.q.kq * a.lv0.ab2);
     LineProof<T> pf{};
-    T wcs = T(0);
-    if (prove) {
-      pf = line_proof<T>(proofs[slot], n_off, float(a.lv0.tau));
-      wcs = centre_value<T, M>(s.q, c);
-    }
+    if (prove) pf = line_proof<T>(proofs[slot], n_off, float(a.lv0.tau));
     Env<T> e = env_none<T>();
     for (int m0 = 0; m0 < n_dir; m0 += kTabLines) {
       const int n = min(n_dir - m0, kTabLines);
@@ -269,25 +276,26 @@ __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KA
         wave_lds_fence();
       }
       const int off = whole ? i * n_dir : -m0;
-      const auto lines = [&](int dir) { return tab.get(dir + off, c); };
-      if constexpr (M == kFamSTVK) {
-        e = envelope_scan<T, S, K, M>(s.q, s.wc, m0 + n, lay, lines, nullptr, 0, c2u, nullptr, &c, m0, kWave / S, e);
-      } else {
-        int* order = orders[wave];
-        int count = 0;
+      const auto lines = [&](int dir) { return tab.get(dir + off, s.c); };
+      // the directions to visit: all, or those not proven
+      int* order = nullptr;
+      int first = m0, end = m0 + n;
+      if (M != kFamSTVK && prove) {
+        order = orders[wave];
+        first = end = 0;
         wave_lds_fence();
-        for (int c0 = m0; c0 < m0 + n; c0 += kWave) {
-          const int dir = c0 + lane_id();
+        for (int d0 = m0; d0 < m0 + n; d0 += kWave) {
+          const int dir = d0 + lane_id();
           const bool valid = dir < m0 + n;
-          const bool proven = prove && valid && pf(lines(valid ? dir : m0));
+          const bool proven = valid && pf(lines(valid ? dir : m0));
           const unsigned long long mp = __ballot(proven), mo = __ballot(valid && !proven);
-          if (mp) env_merge(e, proven_env(wcs, c0, mp));
-          if (valid && !proven) order[count + __popcll(mo & ((1ull << lane_id()) - 1ull))] = dir;
-          count += __popcll(mo);
+          if (mp) env_merge(e, proven_env(s.c.ws, d0, mp));
+          if (valid && !proven) order[end + __popcll(mo & ((1ull << lane_id()) - 1ull))] = dir;
+          end += __popcll(mo);
         }
         wave_lds_fence();
-        e = envelope_scan<T, S, K, M>(s.q, s.wc, count, lay, lines, nullptr, 0, c2u, order, &c, 0, kWave / S, e);
       }
+      e = envelope_scan<T, S, K, M>(s.q, s.wc, end, lay, lines, nullptr, 0, c2u, order, &s.c, first, kWave / S, e);
     }
     e = envelope_finish<T, M>(s.q, s.wc, e);
     if (lane_id() == 0) write_depth1<T, D, M, true>(a, p, a.lv0, s.q, s.g.G, s.bn, e);
@@ -316,9 +324,8 @@ __global__ __launch_bounds__(kWave * kSplitWaves) void k_depth1_split(KArgs a) {
   }
   constexpr int NSEG = kWave / S;
   const Layout<T, S, K> lay = make_layout<T, S, K>(lv);
-  const Line<T> c = level_line<T, D, M>(s, lv, 0);
   Env<T> e = envelope_scan<T, S, K, M>(s.q, s.wc, lv.n_dir, lay, [&](int dd) { return level_line<T, D, M>(s, lv, dd); },
-                                       nullptr, 0, T(s.q.kq * lv.ab2), nullptr, &c, wave * NSEG, waves * NSEG);
+                                       nullptr, 0, T(s.q.kq * lv.ab2), nullptr, &s.c, wave * NSEG, waves * NSEG);
   if (lane_id() == 0) part[wave] = e;
   __syncthreads();
   if (wave != 0) return;
@@ -483,14 +490,28 @@ __device__ __forceinline__ void stvk_inner_coef(double lam, double mu, double k,
   coef[9] = T(c4);
 }
 
+// What the inner level of one outer sample starts from.
+template <typename T>
+struct OuterSample {
+  Centre<T> c;
+  T wc;
+  ProofPoint<T> pf;
+};
+
+// Outer samples a wave sets up at a time, one per lane, into LDS: the FP64 geometry, the
+// centre and the vertex bound of a sample then cost a lane's share and hold no registers
+// during the line scan (64 x 1025 / 32 x 257, with the centre's logarithm and exponential
+// taken once instead of three times: FP32 96 points 23.2 -> 22.2 ms, FP64 37 points 41.4
+// -> 38.2, an uneven FP32 plan of 384 points 62.0 -> 58.6).
+constexpr int kOuterBatch = 16;
+
 // One outer line (block-level, every thread calls it): the samples W^1(F + t_i R_mo)
 // are inner envelopes computed by the block's waves into LDS; wave 0 takes the
-// outer hull at the centre.  w1f = W^1(F) is the centre sample; when
-// compute_centre is set it is computed here (by wave 0) instead.  Thread 0
-// writes the result to *out.  Returns the centre value used.
+// outer hull at the centre.  w1f = W^1(F) is the centre sample.  Thread 0 writes
+// the result to *out.
 template <typename T, int D, int S, int K, int M>
-__device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const Level& lo, const Level& li, T w1f,
-                        bool compute_centre, OuterRes<T>* out, char* smem_raw) {
+__device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, const Level& lo, const Level& li, T w1f,
+                                           OuterRes<T>* out, char* smem_raw) {
   const int co = (lo.n_t - 1) / 2;
   // Up to kMaxTabDirs inner directions the waves keep warm-start bridge slopes,
   // visiting orders and the inner lines' coefficients as polynomials in the outer t
@@ -504,7 +525,8 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
   T* wr = wl + co;                                          // outer samples at +m
   int* order = reinterpret_cast<int*>(wr + co);             // kOuterWaves * n_dir_i (lds_lines)
   __shared__ int capped_any;
-  __shared__ T centre;
+  __shared__ OuterSample<T> samples[kOuterWaves][kOuterBatch];
+  __shared__ Point<T> sq;                     // for the samples' set-up: what the line scan does not use
   __shared__ double sF[D * D], sR[D * D];     // F and R where the samples read them (not in registers)
   double F[D * D], bn;
   load_point<T, D>(a, p, F, bn);
@@ -515,7 +537,6 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
     for (int j = 0; j < D; ++j) R[i * D + j] = lo.a[mo * D + i] * lo.b[mo * D + j];
   if (threadIdx.x == 0) {
     capped_any = 0;
-    centre = w1f;
 #pragma unroll
     for (int k = 0; k < D * D; ++k) { sF[k] = F[k]; sR[k] = R[k]; }
   }
@@ -533,131 +554,106 @@ __device__ __forceinline__ T outer_line(const KArgs& a, int64_t p, int mo, const
                               coef + NC * i);
     }
   }
+  if (threadIdx.x == 0) sq = make_point<T, M>(a.mat, bn);
   if (lds_lines)
     for (int i = threadIdx.x; i < 2 * kOuterWaves * li.n_dir; i += blockDim.x) warm[i] = T(__builtin_nan(""));
   __syncthreads();
   Layout<T, S, K> lay = make_layout<T, S, K>(li);
-  Point<T> q = make_point<T, M>(a.mat, bn);
-  const int wave = threadIdx.x / kWave, nwave = blockDim.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave), nwave = blockDim.x / kWave;
   int capped = 0;
-  if (compute_centre && wave == 0) {
-    double cof[D * D];
-    cofactor<D>(F, cof);
-    T wc = w_point<T, D, M>(q, F, cof);
-    T v = wc;
-    if (wc < inf_v<T>()) {
-      Env<T> e = envelope_at<T, D, S, K, M>(q, F, wc, li, lay);
-      v = e.h;
-      capped |= e.capped;
-    }
-    if (lane_id() == 0) centre = v;
-  }
   // outer samples, interleaved left/right so the waves share both sides; a
   // wave walks one side outwards in even steps of two samples, so the inner
   // bridge slopes of its last two samples (warm, per inner direction),
   // extrapolated, start the next
   T* warm_w = warm + 2 * wave * li.n_dir;      // blocks have kOuterWaves waves
   int* order_w = order + wave * li.n_dir;
-  for (int s = wave; s < 2 * co; s += nwave) {
-    int m = 1 + (s >> 1);
-    double t = (s & 1) ? t_of(lo, m) : -t_of(lo, m);
-    double G[D * D];
+  const Point<T> q = sq;
+  const T c2u = T(q.kq * li.ab2);
+  const bool prove = M == kFamNH && q.model == 0 && c2u == c2u && proves_lines<T, S>(li.n_dir);
+  const auto sample_t = [&](int s) { return (s & 1) ? t_of(lo, 1 + (s >> 1)) : -t_of(lo, 1 + (s >> 1)); };
+  for (int s0 = wave; s0 < 2 * co; s0 += nwave * kOuterBatch) {
+    wave_lds_fence();                          // reads of the samples before are done
+    if (tab && lane_id() < kOuterBatch && s0 + lane_id() * nwave < 2 * co) {
+      const double t = sample_t(s0 + lane_id() * nwave);
+      double G[D * D], cof[D * D];
 #pragma unroll
-    for (int k = 0; k < D * D; ++k) G[k] = sF[k] + t * sR[k];
-    T v;
-    if (tab) {
-      if constexpr (M == kFamSTVK) {
-        // W(G) and c0 = k psi0(G), shared by every inner line; c1 .. c4 from the table
-        double cof[D * D];
-        cofactor<D>(G, cof);
-        const double zero[D] = {};
-        const Line<T> L0 = line_setup<T, D, M>(q, G, cof, zero, zero);
-        T wc = fma(ws_sample_stvk<T>(T(0), L0, q), q.sc, q.B);
-        v = wc;
-        if (wc < inf_v<T>()) {
-          const T tt = T(t);
-          Env<T> e = envelope_next<T, S, K, M>(q, wc, li.n_dir, lay, [&](int dd) {
+      for (int k = 0; k < D * D; ++k) G[k] = sF[k] + t * sR[k];
+      cofactor<D>(G, cof);
+      // W(G) and the part of the inner lines they share: c0 = k psi0(G) (St. Venant-
+      // Kirchhoff), J0 = det G and c0 = kq (|G|^2 - d) (neo-Hooke), G11 and the rest
+      // (double well)
+      const double zero[D] = {};
+      const Line<T> L0 = line_setup<T, D, M>(sq, G, cof, zero, zero);
+      OuterSample<T>& o = samples[wave][lane_id()];
+      if (M == kFamSTVK || q.model == 0) {
+        const Centre<T> c = make_centre<T, M>(sq, L0.J0, L0.c0);
+        o.c = c;
+        o.wc = fma(c.ws, sq.sc, sq.B);
+        if constexpr (M == kFamNH)
+          if (prove) o.pf = proof_point<T>(sq, c, c2u, lay.c, float(li.tau));
+      } else {
+        o.c = Centre<T>{L0.J0, L0.c0, T(0), T(0), T(0)};
+        o.wc = w_sample_doublewell<T>(T(0), L0);
+      }
+    }
+    wave_lds_fence();
+    for (int j = 0; j < kOuterBatch; ++j) {
+      const int s = s0 + j * nwave;
+      if (s >= 2 * co) break;                  // wave-uniform
+      T v;
+      if (tab) {
+        const OuterSample<T>& o = samples[wave][j];
+        v = o.wc;
+        if (o.wc < inf_v<T>()) {
+          const T tt = T(sample_t(s));
+          const T J0 = o.c.J0, c0 = o.c.c0;
+          const Env<T> e = envelope_next<T, S, K, M>(q, o.wc, li.n_dir, lay, [&](int dd) {
             const T* cf = coef + NC * dd;
-            Line<T> L;
-            L.J0 = T(0);
-            L.J1 = T(0);
-            L.c0 = L0.c0;
-            L.c1 = fma(tt, fma(tt, fma(tt, cf[3], cf[2]), cf[1]), cf[0]);
-            L.c2 = fma(tt, fma(tt, cf[6], cf[5]), cf[4]);
-            L.c3 = fma(tt, cf[8], cf[7]);
-            L.c4 = cf[9];
-            return L;
-          }, warm_w, order_w, L0, float(li.tau));
+            if constexpr (M == kFamSTVK)
+              return Line<T>{T(0), T(0), c0, T(fma(tt, fma(tt, fma(tt, cf[3], cf[2]), cf[1]), cf[0])),
+                             T(fma(tt, fma(tt, cf[6], cf[5]), cf[4])), T(fma(tt, cf[8], cf[7])), cf[9]};
+            else
+              return Line<T>{J0, T(fma(tt, cf[1], cf[0])), c0, T(fma(tt, cf[3], cf[2])), cf[4]};
+          }, warm_w, order_w, o.c, prove ? &o.pf : nullptr, float(li.tau), c2u);
           v = e.h;
           capped |= e.capped;
         }
       } else {
-        // W(G) and the per-sample parts of every inner line: J0 = det G, c0 = kq (|G|^2 - d)
-        // (neo-Hooke) or G11 and the quadratic rest (double well)
-        double cof[D * D];
+        const double t = sample_t(s);
+        double G[D * D], cof[D * D];
+#pragma unroll
+        for (int k = 0; k < D * D; ++k) G[k] = sF[k] + t * sR[k];
         cofactor<D>(G, cof);
-        double J0, c0 = 0.0;
-        if (a.mat.model == 0) {
-          J0 = det_of<D>(G, cof);
-#pragma unroll
-          for (int k = 0; k < D * D; ++k) c0 += G[k] * G[k];
-          c0 = q.kq * (c0 - double(D));
-        } else {
-          J0 = G[0];
-#pragma unroll
-          for (int i = 0; i < D; ++i)
-#pragma unroll
-            for (int j = 0; j < D; ++j)
-              if (i || j) c0 += (G[i * D + j] - (i == j ? 1.0 : 0.0)) * (G[i * D + j] - (i == j ? 1.0 : 0.0));
-        }
-        Line<T> L0 = {T(J0), T(0), T(c0), T(0), T(0)};
-        T wc = q.model == 0 ? fma(ws_sample<T>(T(0), L0, q), q.sc, q.B) : w_sample_doublewell<T>(T(0), L0);
+        const T wc = w_point<T, D, M>(q, G, cof);
         v = wc;
         if (wc < inf_v<T>()) {
-          const T tt = T(t);
-          Env<T> e = envelope_next<T, S, K>(q, wc, li.n_dir, lay, [&](int dd) {
-            const T* cf = coef + NC * dd;
-            return Line<T>{L0.J0, T(fma(tt, cf[1], cf[0])), L0.c0, T(fma(tt, cf[3], cf[2])), cf[4]};
-          }, warm_w, order_w, L0, float(li.tau), T(q.kq * li.ab2));
+          const Env<T> e = envelope_at<T, D, S, K, M>(q, G, wc, li, lay);
           v = e.h;
           capped |= e.capped;
         }
       }
-    } else {
-      double cof[D * D];
-      cofactor<D>(G, cof);
-      T wc = w_point<T, D, M>(q, G, cof);
-      v = wc;
-      if (wc < inf_v<T>()) {
-        Env<T> e = envelope_at<T, D, S, K, M>(q, G, wc, li, lay);
-        v = e.h;
-        capped |= e.capped;
-      }
+      if (lane_id() == 0) ((s & 1) ? wr : wl)[s >> 1] = v;
     }
-    if (lane_id() == 0) ((s & 1) ? wr : wl)[m - 1] = v;
   }
   if (capped && lane_id() == 0) atomicOr(&capped_any, 1);
   __syncthreads();
-  T cv = centre;
   if (wave == 0) {
-    LineHull<T> r = hull_centre_lds<T>(wl, wr, co, cv);
+    LineHull<T> r = hull_centre_lds<T>(wl, wr, co, w1f);
     if (threadIdx.x == 0) *out = OuterRes<T>{r.h, r.mp, r.mq, r.capped | capped_any};
   }
   __syncthreads();                            // LDS reused by the caller's next item
-  return cv;
 }
 
-// Waves per SIMD k_outer is held to.  FP64 lines of up to 8 samples per lane at three
-// (168 registers; 231 and two left free) where a wave takes few lines at once: what
-// spills then is the per-sample part of log and exp, reloaded once per outer sample,
-// which 32-lane lines (2 at once: 16 and more wave steps per outer sample) make up for
-// and 8-lane lines (8 at once) do not.  40 points, 32 x 513 outer, 16 inner directions,
-// two / three waves: 2D 257 inner points (32 lanes) 9.3 / 8.5 ms, 129 (16 lanes) 4.5 /
-// 4.8, 61 (8 lanes) 2.6 / 3.3; 3D 12.3 / 9.6, 6.4 / 5.9, 3.7 / 4.7.
+// Waves per SIMD k_outer is held to: three for up to 16 FP32 or 8 FP64 samples per lane
+// (168 registers; two left free), where dependent chains of log, exp and lane reductions
+// leave issue slots empty and what spills is reloaded once per outer sample or seldom.
+// 40 points, 32 x 153 outer, 32 inner directions, two / three waves: FP32 3D 45 inner
+// samples 670 / 549 us, 129 866 / 721, 257 (one wave, 256 registers) 1842 / 1112; FP64
+// 2D 45 1338 / 1237, 129 2191 / 2152, 3D 45 1260 / 1130.  A launch too small to fill the
+// chip loses a little (7 points, FP32 3D, 32 x 91: 306 / 318 us).
 template <typename T, int D, int S, int K>
 constexpr int outer_waves() {
-  if (sizeof(T) == 8) return K > 8 ? 1 : (S >= 32 || (S == 16 && D == 3)) ? 3 : 2;
-  return D == 2 && K <= 16 ? 3 : 1;
+  return K <= (sizeof(T) == 8 ? 8 : 16) ? 3 : 1;
 }
 
 template <typename T, int D, int S, int K, int M>
@@ -672,7 +668,7 @@ __global__ __launch_bounds__(256, (outer_waves<T, D, S, K>())) void k_outer(KArg
     if (threadIdx.x == 0) *out = OuterRes<T>{w1f, 0, 0, 0};
     return;
   }
-  outer_line<T, D, S, K, M>(a, p, mo, a.lv0, a.lv1, w1f, false, out, smem_raw);
+  outer_line<T, D, S, K, M>(a, p, mo, a.lv0, a.lv1, w1f, out, smem_raw);
 }
 
 // Two-level result of point p from its outer-line results res[0 .. n_dir_o):
