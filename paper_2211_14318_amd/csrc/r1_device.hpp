@@ -486,7 +486,6 @@ template <typename T>
 struct LineHull {
   T h;
   int mp, mq;
-  int capped;
 };
 
 // Per-lane constants of a line layout: offsets m_h = 1 + sl + S*h and t_h = tau*2m/(n_t-1)
@@ -627,8 +626,8 @@ __device__ __forceinline__ void bridge_alternating(const T (&w)[K], const T (&wc
 
 // Slope iteration for the bridge over the centre (see hull_centre) on the
 // segments with todo set, from slope s: on return those that converged have
-// todo cleared, the pair (mp, mq), the tilted minima (ep, eq) and the slope s
-// of the last pass.  A pass at any slope bounds the hull value at the centre
+// todo cleared, the pair (mp, mq) and the slope s of the last pass; (ep, eq) are
+// the last pass's tilted minima.  A pass at any slope bounds the hull value at the centre
 // from below by min(ep, eq, wc) (the line of that slope through the lowest
 // tilted sample lies under every sample); a segment whose bound exceeds thr
 // stops there too, with the pair and tilted minima of that pass, whose chord
@@ -664,6 +663,7 @@ __device__ __forceinline__ void slope_bridge(const T (&w)[K], const Layout<T, S,
         mp = mpn; mq = mqn;
         ep = epn; eq = eqn;
       } else {
+        if (pass + 1 == kSlopePasses) { ep = epn; eq = eqn; }
         mp = mpn; mq = mqn;
         s = s + key_div(eqn - epn, T(mq + mp));
       }
@@ -694,7 +694,8 @@ __device__ __forceinline__ void slope_bridge(const T (&w)[K], const Layout<T, S,
 //
 // thr: a line whose hull value at the centre is shown to exceed it may return
 // an upper bound above thr instead (see slope_bridge); +inf: exact for every
-// line.
+// line.  cap: lowered to a value that the line's hull value is not below where its
+// search ends at the iteration cap (h is then an upper bound only).
 //
 // hot (wave-uniform): every line of the wave has a warm start.  The vertex
 // test is then skipped: the centre is a vertex exactly when the bridge of the
@@ -703,11 +704,10 @@ __device__ __forceinline__ void slope_bridge(const T (&w)[K], const Layout<T, S,
 // standard path instead.
 template <typename T, int S, int K>
 __device__ __forceinline__ LineHull<T> hull_centre(const T (&w)[K], T wc, const T (&wci)[K / 2],
-                                                   const Layout<T, S, K>& lay, T& sig, bool hot,
-                                                   T thr = inf_v<T>()) {
+                                                   const Layout<T, S, K>& lay, T& sig, bool hot, T thr, T& cap) {
   constexpr int H = K / 2;
   LineHull<T> r;
-  r.h = wc; r.mp = 0; r.mq = 0; r.capped = 0;
+  r.h = wc; r.mp = 0; r.mq = 0;
   const T nan = T(__builtin_nan(""));
   if (hot) {
     bool todo = true;
@@ -757,7 +757,12 @@ __device__ __forceinline__ LineHull<T> hull_centre(const T (&w)[K], T wc, const 
   if (__any(todo)) {
     // slope budget spent (not seen in practice): finish with the alternating search
     T wp = T(0), wq = T(0);
-    bridge_alternating<T, S, K>(w, wci, lay, todo, mp, wp, mq, wq, r.capped);
+    // the last pass bounds the hull value from below; its slope is by then within rounding
+    // of the best one where the alternating search does not end either
+    const T low = fmin(fmin(ep, eq), wc);
+    int capped = 0;
+    bridge_alternating<T, S, K>(w, wci, lay, todo, mp, wp, mq, wq, capped);
+    if (capped) cap = fmin(cap, low);
     if (todo) {       // express its result in the tilted form used below
       s = key_div(wq - wp, T(mq + mp));
       ep = fma(s, T(mp), wp);
@@ -850,7 +855,7 @@ template <typename T>
 struct Env {            // W^1 at a point: value, direction, bracketing offsets
   T h;
   int dir, mp, mq;
-  int capped;
+  T cap;                // the least cap of its lines
   T second;             // runner-up over directions (the smallest value of another direction)
 };
 
@@ -866,15 +871,24 @@ __device__ __forceinline__ bool near_tie(const Env<T>& e) {
   return (e.mp + e.mq) > 0 && e.second - e.h <= tie_margin<T>() * fmax(fabs(e.h), tie_floor<T>());
 }
 
+// Whether a bridge search hit its cap on a line that may hold the minimum: one whose
+// hull value is not shown to lie above it by more than the tie margin.  (Others would
+// be reported or not with the order of the directions and their split over waves, since
+// a search that is shown to lie above the best value known at its turn stops early.)
 template <typename T>
-__device__ __forceinline__ Env<T> env_none() { return {inf_v<T>(), 0, 0, 0, 0, inf_v<T>()}; }
+__device__ __forceinline__ bool capped(const Env<T>& e) {
+  return e.cap <= e.h + tie_margin<T>() * fmax(fabs(e.h), tie_floor<T>());
+}
+
+template <typename T>
+__device__ __forceinline__ Env<T> env_none() { return {inf_v<T>(), 0, 0, 0, inf_v<T>(), inf_v<T>()}; }
 
 // Merges another set of directions' result into a (lexicographic in value, direction).
 template <typename T>
 __device__ __forceinline__ void env_merge(Env<T>& a, const Env<T>& o) {
   const bool take = o.h < a.h || (o.h == a.h && o.dir < a.dir);
   a.second = take ? fmin(o.second, a.h) : fmin(a.second, o.h);
-  a.capped |= o.capped;
+  a.cap = fmin(a.cap, o.cap);
   if (take) { a.h = o.h; a.dir = o.dir; a.mp = o.mp; a.mq = o.mq; }
 }
 
@@ -1011,7 +1025,7 @@ __device__ __forceinline__ LineProof<T> line_proof(const ProofPoint<T>& f, int n
 // is the centre value wcs.
 template <typename T>
 __device__ __forceinline__ Env<T> proven_env(T wcs, int base, unsigned long long mask) {
-  return {wcs, base + __ffsll(mask) - 1, 0, 0, 0, (mask & (mask - 1)) ? wcs : inf_v<T>()};
+  return {wcs, base + __ffsll(mask) - 1, 0, 0, inf_v<T>(), (mask & (mask - 1)) ? wcs : inf_v<T>()};
 }
 
 // One lamination level at a point (wave-uniform): min over n directions of the line
@@ -1120,7 +1134,7 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
       sg = s2 == s2 ? fma(T(2), s1, -s2) : s1;
     }
     const bool hot = warm && __all(act && s1 == s1);
-    LineHull<T> lh = hull_centre<T, S, K>(w, wcs, wci, lay, sg, hot, thr);
+    LineHull<T> lh = hull_centre<T, S, K>(w, wcs, wci, lay, sg, hot, thr, best.cap);
     if (warm && act && (lane & (S - 1)) == 0) {
       warm[n_warm + dir] = sg == sg ? s1 : sg;
       warm[dir] = sg;
@@ -1133,8 +1147,9 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
         best.second = fmin(best.second, lh.h);
       }
     }
-    best.capped |= lh.capped;
   }
+  // a warm search is never stopped early: every one that is capped is reported
+  if (warm && best.cap < inf_v<T>()) best.cap = -inf_v<T>();
   // across segments: lexicographic (value, direction)
 #pragma unroll
   for (int off = S; off < kWave; off <<= 1) {
@@ -1143,7 +1158,7 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
     o.dir = __shfl_xor(best.dir, off, kWave);
     o.mp = __shfl_xor(best.mp, off, kWave);
     o.mq = __shfl_xor(best.mq, off, kWave);
-    o.capped = __shfl_xor(best.capped, off, kWave);
+    o.cap = __shfl_xor(best.cap, off, kWave);
     o.second = __shfl_xor(best.second, off, kWave);
     env_merge(best, o);
   }
@@ -1157,6 +1172,7 @@ __device__ __forceinline__ Env<T> envelope_finish(const Point<T>& q, T wc, Env<T
   if (M == kFamSTVK || q.model == 0) {
     best.h = (best.mp + best.mq) ? fma(best.h, q.sc, q.B) : wc;
     best.second = fma(best.second, q.sc, q.B);
+    best.cap = fma(best.cap, q.sc, q.B);
   }
   return best;
 }

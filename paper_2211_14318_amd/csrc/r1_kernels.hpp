@@ -63,7 +63,7 @@ __device__ Env<T> envelope_with_stress(const KArgs& a, const Level& lv, const La
   double cof[D * D];
   cofactor<D>(G, cof);
   T wc = w_point<T, D, M>(q, G, cof);
-  Env<T> e = {wc, 0, 0, 0, 0, inf_v<T>()};
+  Env<T> e = {wc, 0, 0, 0, inf_v<T>(), inf_v<T>()};
   if (wc < inf_v<T>()) e = envelope_at<T, D, S, K, M>(q, G, wc, lv, lay);
   double Gm[D * D], Gp[D * D], Pm[D * D], Pp[D * D];
   line_point<D>(G, lv, e.dir, -t_of(lv, e.mp), Gm);
@@ -166,7 +166,7 @@ __device__ __forceinline__ void write_depth1(const KArgs& a, int64_t p, const Le
     a.tree[p * R1_TREE_NODES] = r1_laminate{e.dir, c - e.mp, c + e.mq, xi};
     for (int k = 1; k < R1_TREE_NODES; ++k) a.tree[p * R1_TREE_NODES + k] = r1_laminate{0, 0, 0, 1.0f};
   }
-  if (a.flags) a.flags[p] = (e.capped ? R1_PT_ITERCAP : 0) | (near_tie(e) ? R1_PT_TIE : 0);
+  if (a.flags) a.flags[p] = (capped(e) ? R1_PT_ITERCAP : 0) | (near_tie(e) ? R1_PT_TIE : 0);
 }
 
 // One-level envelope of point p on level lv with stress, tree and flags as
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(256) void k_stress1(KArgs a) {
 // the samples at offsets -m / +m, m = 1..c (NaN or +inf = absent).  Same search
 // as hull_centre: a values-only vertex test, then alternating tangent queries.
 template <typename T>
-__device__ LineHull<T> hull_centre_lds(const T* wl, const T* wr, int c, T wc) {
+__device__ LineHull<T> hull_centre_lds(const T* wl, const T* wr, int c, T wc, int* capped) {
   const int lane = lane_id();
   T maxL = -inf_v<T>(), minR = inf_v<T>();
   for (int m = 1 + lane; m <= c; m += kWave) {
@@ -394,7 +394,8 @@ __device__ LineHull<T> hull_centre_lds(const T* wl, const T* wr, int c, T wc) {
   }
   maxL = seg_max<kWave>(maxL);
   minR = seg_min<kWave>(minR);
-  LineHull<T> r = {wc, 0, 0, 0};
+  LineHull<T> r = {wc, 0, 0};
+  *capped = 0;
   if (!(maxL >= minR)) return r;      // wave-uniform
   Cand<T> p = {-inf_v<T>(), 0, T(0)};
   for (int m = 1 + lane; m <= c; m += kWave) {
@@ -430,7 +431,7 @@ __device__ LineHull<T> hull_centre_lds(const T* wl, const T* wr, int c, T wc) {
     p = pc;
   }
   r.h = (T(q.m) * p.w + T(p.m) * q.w) / T(q.m + p.m);
-  r.mp = p.m; r.mq = q.m; r.capped = 1;
+  r.mp = p.m; r.mq = q.m; *capped = 1;
   return r;
 }
 
@@ -560,7 +561,7 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
   __syncthreads();
   Layout<T, S, K> lay = make_layout<T, S, K>(li);
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave), nwave = blockDim.x / kWave;
-  int capped = 0;
+  int cap = 0;
   // outer samples, interleaved left/right so the waves share both sides; a
   // wave walks one side outwards in even steps of two samples, so the inner
   // bridge slopes of its last two samples (warm, per inner direction),
@@ -616,7 +617,7 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
               return Line<T>{J0, T(fma(tt, cf[1], cf[0])), c0, T(fma(tt, cf[3], cf[2])), cf[4]};
           }, warm_w, order_w, o.c, prove ? &o.pf : nullptr, float(li.tau), c2u);
           v = e.h;
-          capped |= e.capped;
+          cap |= e.cap < inf_v<T>();
         }
       } else {
         const double t = sample_t(s);
@@ -629,17 +630,18 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
         if (wc < inf_v<T>()) {
           const Env<T> e = envelope_at<T, D, S, K, M>(q, G, wc, li, lay);
           v = e.h;
-          capped |= e.capped;
+          cap |= capped(e);
         }
       }
       if (lane_id() == 0) ((s & 1) ? wr : wl)[s >> 1] = v;
     }
   }
-  if (capped && lane_id() == 0) atomicOr(&capped_any, 1);
+  if (cap && lane_id() == 0) atomicOr(&capped_any, 1);
   __syncthreads();
   if (wave == 0) {
-    LineHull<T> r = hull_centre_lds<T>(wl, wr, co, w1f);
-    if (threadIdx.x == 0) *out = OuterRes<T>{r.h, r.mp, r.mq, r.capped | capped_any};
+    int own;
+    LineHull<T> r = hull_centre_lds<T>(wl, wr, co, w1f, &own);
+    if (threadIdx.x == 0) *out = OuterRes<T>{r.h, r.mp, r.mq, own | capped_any};
   }
   __syncthreads();                            // LDS reused by the caller's next item
 }
@@ -704,7 +706,7 @@ __device__ __forceinline__ void finalize_point(const KArgs& a, int64_t p, const 
     bs = take ? fmin(os, bh) : fmin(bs, oh);
     bh = take ? oh : bh; bd = take ? od : bd; bp = take ? op : bp; bq = take ? oq : bq;
   }
-  bool tie = near_tie(Env<T>{bh, bd, bp, bq, 0, bs});
+  bool tie = near_tie(Env<T>{bh, bd, bp, bq, inf_v<T>(), bs});
   const int c = (lo.n_t - 1) / 2, ci = (li.n_t - 1) / 2;
   r1_laminate node[3];
   double Pout[D * D];
@@ -714,12 +716,12 @@ __device__ __forceinline__ void finalize_point(const KArgs& a, int64_t p, const 
     line_point<D>(F, lo, bd, -t_of(lo, bp), Gm);
     line_point<D>(F, lo, bd, t_of(lo, bq), Gp);
     Env<T> em = envelope_with_stress<T, D, S, K, M>(a, li, lay, bn, Gm, Pm);
-    cap |= em.capped;
+    cap |= capped(em);
     tie = tie || near_tie(em);
     Env<T> ep = em;
     if (bp + bq) {
       ep = envelope_with_stress<T, D, S, K, M>(a, li, lay, bn, Gp, Pp);
-      cap |= ep.capped;
+      cap |= capped(ep);
       tie = tie || near_tie(ep);
     } else {
 #pragma unroll

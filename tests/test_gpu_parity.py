@@ -327,3 +327,30 @@ def test_lines_left_unsampled_in_two_levels(lib, kind, mat, beta_max):
     g = run_gpu(lib, cfg, kind)
     _, _, W, _, _ = run_oracle(cfg, g["F_in"], g["bn_in"], want_tree=False)
     assert PA.energy_errors(g["W"], W, kind).max() <= PA.RTOL[kind]
+
+
+@pytest.mark.parametrize("dim,drawn,beta_max,first,n,at", [(3, 40_000, 0.2, 20_480, 19_520, (23_656, 37_159)),
+                                                           (2, 200_000, 1.1, 32_768, 20_000, (44_024,))])
+def test_iteration_cap_flag_does_not_depend_on_the_batch(lib, dim, drawn, beta_max, first, n, at):
+    """FP32 lines of 2049 samples on which bridge searches run into their cap (at the 3D
+    points on lines that cannot hold the minimum, at the 2D point on one that may): one
+    large batch, the same points in slices of 4096 (several waves per point) and in small
+    batches report the same flags."""
+    rng = np.random.default_rng(77)
+    G = np.eye(dim) + (0.3 if dim == 2 else 0.2) * rng.standard_normal((drawn, dim, dim))
+    bad = np.linalg.det(G) < 0.05
+    G[bad] = np.eye(dim) + 0.05 * rng.standard_normal((int(bad.sum()), dim, dim))
+    F, bn = G.reshape(drawn, -1).T, rng.uniform(0.0, beta_max, drawn)
+    cfg = WL.small_random(dim, 1, (8, 8), 2049)
+
+    def flags(i, m):
+        m = min(m, first + n - i)
+        return run_gpu(lib, dict(cfg, n=m, F=F[:, i:i + m].copy(), beta_n=bn[i:i + m].copy()), "f32")["flags"]
+
+    full = flags(first, n)
+    few = np.concatenate([flags(i, 4096) for i in range(first, first + n, 4096)])
+    assert np.array_equal(full, few), np.nonzero(full != few)[0] + first
+    for p in at:
+        assert bool(full[p - first] & 8) == (dim == 2)
+        for m in (1, 9, 300):
+            assert np.array_equal(flags(p, m), full[p - first:p - first + m]), (p, m)
