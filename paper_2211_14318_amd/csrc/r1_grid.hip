@@ -454,8 +454,8 @@ __device__ __forceinline__ long long list_entry(const PickDir& d) {
 }
 
 // lists[M * pitch ..]: the entries of dirs that a node with interior mask M looks
-// at, in order, filled up to a multiple of kPickBatch with steps of 0 (the node is
-// its own neighbour, which lowers nothing); counts[M] their number.  One wave per mask.
+// at, in order, filled up to a multiple of kPickBatch with steps of 0 and no slot, which
+// hold no candidate; counts[M] their number.  One wave per mask.
 __global__ __launch_bounds__(64) void k_grid_lists(const PickDir* __restrict__ dirs, int ne, int pitch,
                                                    long long* __restrict__ lists, int* __restrict__ counts) {
   const uint32_t M = blockIdx.x;
@@ -556,8 +556,9 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, Guard guard, int 
           const uint32_t code = uint32_t(e[j] >> 32), slot1 = code & 31u;
           // the monotone chain on three nodes: the middle one is popped exactly when
           // it lies on or above the chord, and its candidate is the chord's midpoint
-          // (an absent neighbour, +inf or NaN, fails the comparisons)
-          const bool cut = w0 - a[j] >= b[j] - w0;
+          // (an absent neighbour, +inf or NaN, fails the comparisons; a filling entry has
+          // none: the midpoint of w0 and w0 is -inf where their sum overflows)
+          const bool cut = int32_t(e[j]) != 0 && w0 - a[j] >= b[j] - w0;
           const bool ok = slot1 ? ((mk >> (slot1 - 1u)) & 1u) != 0u : cut;
           const T c = slot1 ? a[j] : (a[j] + b[j]) / T(2);
           if (ok && c < lim) take(c, int(code >> 5), int(slot1) - 1);

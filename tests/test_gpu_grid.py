@@ -516,3 +516,23 @@ def test_grid_double_well_tangent_on_gpu(lib):
             F11 = O.grid_node(og, p)[0, 0]
             ref = np.diag([8.0 if abs(F11) < 1.0 else 12.0 * F11 ** 2 - 4.0, 2.0, 2.0, 2.0]).ravel()
             assert np.max(np.abs(Ag[:, p] - ref)) < tol * 50, (dt, F11)
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_grid_nodes_near_the_lowest_value_of_the_type(lib, kind, dim):
+    """A node value whose double overflows, at nodes that are the middle of one, two or three
+    lines (or of none): it is no candidate of its own.  One iteration equals the oracle's."""
+    r1, h, torch = lib
+    dt = torch.float64 if kind == "f64" else torch.float32
+    n = (3,) * (dim * dim)
+    g, og = both_grids(r1, dim, n, (0.0,) * (dim * dim), 0.1)
+    for at in ((1, 0, 0), (0, 1, 0), (0, 0, 0), (1, 1, 0), (1, 1, 1)):
+        W0 = np.zeros(n)
+        p = (at + (0,) * (dim * dim - 3)) if dim == 3 else at + (0,)
+        W0[p] = -0.8 * torch.finfo(dt).max
+        W = torch.tensor(W0.ravel(), dtype=dt, device="cuda")
+        ref, _ = O.grid_sweep(og, O.grid_r11(dim), W.double().cpu().numpy())
+        h.grid_laminate(g, r1.grid_r11(dim), W, k_max=1, tol=0.0)
+        Wg = W.double().cpu().numpy()
+        assert np.isfinite(Wg).all() and np.array_equal(Wg, ref), at
