@@ -536,3 +536,11 @@ def test_grid_nodes_near_the_lowest_value_of_the_type(lib, kind, dim):
         h.grid_laminate(g, r1.grid_r11(dim), W, k_max=1, tol=0.0)
         Wg = W.double().cpu().numpy()
         assert np.isfinite(Wg).all() and np.array_equal(Wg, ref), at
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("n", [(129, 1, 3, 40), (149, 1, 3, 40), (149, 2, 1, 151)])
+def test_grid_lines_beyond_128_nodes(lib, kind, n):
+    """Lines on both sides of the longest that are staged in LDS (FP32: 149 nodes), alone and
+    beside longer ones, as in test_grid_every_hull_path_on_random_values."""
+    test_grid_every_hull_path_on_random_values(lib, kind, n)
