@@ -47,6 +47,11 @@ __device__ __forceinline__ double lg_t(double x) { return r1x::log_pos(x); }
 __device__ __forceinline__ float expk(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ double expk(double x) { return r1x::exp_core(fmax(x, -746.0)); }
 
+// The hardware reciprocal in the argument's own type and range (relative error below
+// 2^-22), for margins.
+__device__ __forceinline__ float rcp_t(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double rcp_t(double x) { return __builtin_amdgcn_rcp(x); }
+
 struct Material {
   int dim, model;        // model: 0 neo-Hooke damage, 1 double-well test energy, 2 St. Venant-Kirchhoff damage
   double mu, lambda, D_inf, D0;
@@ -1123,7 +1128,7 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
       if (bw < inf_v<T>()) {
         const T bW = scaled ? fma(bw, q.sc, q.B) : bw;
         const T mW = T(2) * tie_margin<T>() * fmax(fabs(bW), tie_floor<T>());
-        thr = bw + (scaled ? mW * T(__builtin_amdgcn_rcpf(float(q.sc))) : mW);
+        thr = bw + (scaled ? mW * rcp_t(q.sc) : mW);
       }
     }
     T sg = T(__builtin_nan("")), s1 = sg;

@@ -354,3 +354,25 @@ def test_iteration_cap_flag_does_not_depend_on_the_batch(lib, dim, drawn, beta_m
         assert bool(full[p - first] & 8) == (dim == 2)
         for m in (1, 9, 300):
             assert np.array_equal(flags(p, m), full[p - first:p - first + m]), (p, m)
+
+
+@pytest.mark.parametrize("dim,dirs", [(2, (8, 8)), (3, (8, 8))])
+def test_fp64_results_scale_with_the_moduli(lib, dim, dirs):
+    """Moduli, threshold scale and history times 2^20 or 2^180 (beyond what FP32 can hold):
+    the energies scale by the same power, laminates and flags are the same bits.  Points of
+    isotropic stretch, disturbed by 1e-12 .. 1e-9, whose directions nearly tie, among
+    random ones."""
+    cfg = WL.small_random(dim, 600, dirs, 129, tau=1.0, sigma=0.3 if dim == 2 else 0.2, seed_tag=960 + dim)
+    rng = np.random.default_rng(7)
+    iso = np.eye(dim).reshape(-1, 1) * rng.uniform(1.1, 1.6, 400)
+    cfg["F"][:, :400] = iso + 10.0 ** rng.uniform(-12, -9, 400) * rng.standard_normal((dim * dim, 400))
+    res = []
+    for k in (20, 180):
+        f = 2.0 ** k
+        mat = {n: (v if n == "D_inf" else v * f) for n, v in cfg["material"].items()}
+        res.append((f, run_gpu(lib, dict(cfg, material=mat, beta_n=cfg["beta_n"] * f), "f64")))
+    (f0, a), (f1, b) = res
+    assert np.array_equal(a["W"] / f0, b["W"] / f1)
+    assert np.array_equal(a["tree"], b["tree"])
+    assert np.array_equal(a["flags"], b["flags"]), int((a["flags"] != b["flags"]).sum())
+    assert (a["flags"] & 16).sum() >= 16 * 20 and (a["flags"] & 16 == 0).sum() >= 20
