@@ -336,28 +336,34 @@ __global__ __launch_bounds__(kWave * kSplitWaves) void k_depth1_split(KArgs a) {
 }
 
 // Waves per point of a one-level launch of n points: 1 (k_depth1) or 2 .. kSplitWaves
-// (k_depth1_split).  A wave's time is its line steps (steps / w) and about 1.25 steps
-// of set-up, for every round of waves the chip holds at once, and half a step count of
-// tail where there are several rounds; w minimises that.  Measured (us; w = 1, 2, 4, 8;
-// * the choice), FP64 2D 16 x 201: 64 points 41 23 15 13*, 512: 41 28 20* 25, 2048: 53*
-// 54 61 87; FP64 3D 64 x 257: 64: 107 60 35 31*, 1024: 120 85* 91 109; FP32 3D 256 x 513:
-// 128: 143 78 43 36*, 1024: 147 113 110* 132; FP32 2D 128 x 1025: 4096: 415 399 363* 395.
-// Beyond kSplitPoints the chip is full and k_depth1's shared set-up wins.
-constexpr int64_t kSplitPoints = 8192;
-inline int one_level_waves(int64_t n, int n_dir, int lines_at_once, int resident) {
-  if (n > kSplitPoints) return 1;
-  const int steps = (n_dir + lines_at_once - 1) / lines_at_once;
-  int best = 1;
-  double best_cost = 0.0;
-  for (int w = 1; w <= kSplitWaves && w <= steps; w *= 2) {
-    const double own = double(steps) / w, rounds = double(n) * w / resident;
-    const double cost = rounds > 1.0 ? rounds * (own + 1.25) + 0.5 * own : own + 1.25;
-    if (w == 1 || cost < best_cost) {
-      best = w;
-      best_cost = cost;
-    }
-  }
-  return best;
+// (k_depth1_split).  More waves per point shorten a point's serial loop of line steps
+// until the chip is full; what a split point repeats (its set-up on every wave, the lines'
+// coefficients on every lane of a step) then costs more than it gains, the sooner the
+// fewer steps it has to share.  Hence bounds on the launch's waves by the number of steps:
+// for 4 waves a point 3 to 16 per SIMD (1024 SIMDs), for 8 less, since a SIMD holds two of
+// such a block where a lane takes more than 128 registers, and for 2, which leave most of
+// the loop, little beyond one.  3D neo-Hooke lines are mostly proven not to need sampling
+// by k_depth1, which the split does not do: it is left earlier there.
+// Measured over 1,300 launches (n 64 .. 8192, 16 .. 400 directions, 65 .. 1025 samples): the
+// choice takes 0.8% more than the best of 1, 2, 4 and 8 in the mean (a model of rounds of
+// waves the chip holds at once 5%).  us for w = 1, 2, 4, 8, * the choice: FP64 2D 16 x 129,
+// 512 points 23 16 13* 17; FP64 3D 64 x 257, 4096: 204* 253 260 366; FP32 3D 256 x 513,
+// 8192: 565* 735 717 1051, 256 x 1025, 300: 348 231 134 117*; FP32 2D 256 x 1025, 4096:
+// 830 734 654* 684; FP64 2D St. Venant-Kirchhoff 64 x 257, 2500: 130 113* 110 156, 256 x 257,
+// 6000: 814 771* 741 1112.
+template <typename T, int D, int S, int K, int M>
+inline int one_level_waves(int64_t n, int n_dir) {
+  const int steps = (n_dir + kWave / S - 1) / (kWave / S);
+  constexpr bool light = sizeof(T) == 4 && M == kFamNH && (K <= 8 || D == 2);   // registers: 4 waves a SIMD
+  const int64_t four = steps <= 8    ? (light ? 4096 : 3072)
+                       : steps <= 32 ? (light ? 8192 : 6144)
+                                     : (D == 3 && M == kFamNH ? 6400 : 16384);
+  const int64_t eight = light ? 4096 : steps <= 32 ? 2048 : 2560;
+  constexpr bool stvk2 = D == 2 && M == kFamSTVK;
+  const int64_t two = stvk2 && sizeof(T) == 8 && steps > 32 ? 16384 : light || stvk2 ? 5000 : 3072;
+  int w = 8 * n <= eight ? kSplitWaves : 4 * n <= four ? 4 : 2 * n <= two ? 2 : 1;
+  while (w > steps) w /= 2;
+  return w;
 }
 
 // Laminate stress of the one-level points (eq. 5.2 on the one-level tree of
@@ -762,12 +768,11 @@ hipError_t launch_T(const KArgs& a, int depth, hipStream_t st, KTimer* tm) {
   dim3 blk(256);
   unsigned per = 256 / kWave;
   const int ppw = one_level_points_per_wave(a.n);
-  const int resident = sizeof(T) == 4 && K <= 16 ? 4096 : 2048;   // waves the chip holds at 4 / 2 per SIMD
   const dim3 grd1(unsigned((a.n + 4 * ppw - 1) / (4 * ppw)));
   if (depth == 1) {
     KArgs a1 = a;
     a1.pts_per_wave = ppw;
-    const int wpp = one_level_waves(a.n, a.lv0.n_dir, kWave / S, resident);
+    const int wpp = one_level_waves<T, D, S, K, M>(a.n, a.lv0.n_dir);
     if (tm) tm->begin("depth1", st);
     if (wpp > 1) {
       hipLaunchKernelGGL((k_depth1_split<T, D, S, K, M>), dim3(unsigned(a.n)), dim3(kWave * wpp), 0, st, a);
@@ -790,7 +795,7 @@ hipError_t launch_T(const KArgs& a, int depth, hipStream_t st, KTimer* tm) {
   pre.want_stress = 0;
   pre.pts_per_wave = ppw;
   dim3 grd(unsigned((a.n + per - 1) / per));
-  const int wpp = one_level_waves(a.n, a.lv1.n_dir, kWave / S, resident);
+  const int wpp = one_level_waves<T, D, S, K, M>(a.n, a.lv1.n_dir);
   if (tm) tm->begin("depth2_centre", st);
   if (wpp > 1)
     hipLaunchKernelGGL((k_depth1_split<T, D, S, K, M>), dim3(unsigned(a.n)), dim3(kWave * wpp), 0, st, pre);
