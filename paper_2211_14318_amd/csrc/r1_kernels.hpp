@@ -501,7 +501,7 @@ __device__ __forceinline__ void stvk_inner_coef(double lam, double mu, double k,
 template <typename T>
 struct OuterSample {
   Centre<T> c;
-  T wc;
+  T wc, t;
   ProofPoint<T> pf;
 };
 
@@ -515,8 +515,8 @@ constexpr int kOuterBatch = 16;
 // One outer line (block-level, every thread calls it): the samples W^1(F + t_i R_mo)
 // are inner envelopes computed by the block's waves into LDS; wave 0 takes the
 // outer hull at the centre.  w1f = W^1(F) is the centre sample.  Thread 0 writes
-// the result to *out.
-template <typename T, int D, int S, int K, int M>
+// the result to *out.  kProve: proven inner lines may be left out (proves_lines).
+template <typename T, int D, int S, int K, int M, bool kProve = true>
 __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, const Level& lo, const Level& li, T w1f,
                                            OuterRes<T>* out, char* smem_raw) {
   const int co = (lo.n_t - 1) / 2;
@@ -576,7 +576,7 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
   int* order_w = order + wave * li.n_dir;
   const Point<T> q = sq;
   const T c2u = T(q.kq * li.ab2);
-  const bool prove = M == kFamNH && q.model == 0 && c2u == c2u && proves_lines<T, S>(li.n_dir);
+  const bool prove = kProve && M == kFamNH && q.model == 0 && c2u == c2u && proves_lines<T, S>(li.n_dir);
   const auto sample_t = [&](int s) { return (s & 1) ? t_of(lo, 1 + (s >> 1)) : -t_of(lo, 1 + (s >> 1)); };
   for (int s0 = wave; s0 < 2 * co; s0 += nwave * kOuterBatch) {
     wave_lds_fence();                          // reads of the samples before are done
@@ -592,6 +592,7 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
       const double zero[D] = {};
       const Line<T> L0 = line_setup<T, D, M>(sq, G, cof, zero, zero);
       OuterSample<T>& o = samples[wave][lane_id()];
+      o.t = T(t);
       if (M == kFamSTVK || q.model == 0) {
         const Centre<T> c = make_centre<T, M>(sq, L0.J0, L0.c0);
         o.c = c;
@@ -612,7 +613,7 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
         const OuterSample<T>& o = samples[wave][j];
         v = o.wc;
         if (o.wc < inf_v<T>()) {
-          const T tt = T(sample_t(s));
+          const T tt = o.t;
           const T J0 = o.c.J0, c0 = o.c.c0;
           const Env<T> e = envelope_next<T, S, K, M>(q, o.wc, li.n_dir, lay, [&](int dd) {
             const T* cf = coef + NC * dd;
@@ -657,15 +658,20 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
 // leave issue slots empty and what spills is reloaded once per outer sample or seldom.
 // 40 points, 32 x 153 outer, 32 inner directions, two / three waves: FP32 3D 45 inner
 // samples 670 / 549 us, 129 866 / 721, 257 (one wave, 256 registers) 1842 / 1112; FP64
-// 2D 45 1338 / 1237, 129 2191 / 2152, 3D 45 1260 / 1130.  A launch too small to fill the
-// chip loses a little (7 points, FP32 3D, 32 x 91: 306 / 318 us).
-template <typename T, int D, int S, int K>
-constexpr int outer_waves() {
-  return K <= (sizeof(T) == 8 ? 8 : 16) ? 3 : 1;
+// 2D 45 1338 / 1237, 129 2191 / 2152, 3D 45 1260 / 1130.  A launch of at most two blocks
+// per CU (kFewBlocks) has no third wave to take, so there the spills only cost: it is held
+// to two waves, and in FP32 it samples every line, since the bound's latency is then not
+// hidden either (64 x 513 outer, four points, three waves with the bound / two without:
+// 2D 32 x 257 1603 / 1553 us, 3D 32 x 129 887 / 843, 16 x 91 543 / 499; FP64 3D 32 x 65,
+// with the bound, 1475 / 1371).
+template <typename T, int K>
+constexpr int outer_waves(bool few) {
+  return K <= (sizeof(T) == 8 ? 8 : 16) ? (few ? 2 : 3) : 1;
 }
+constexpr int64_t kFewBlocks = 512;
 
-template <typename T, int D, int S, int K, int M>
-__global__ __launch_bounds__(256, (outer_waves<T, D, S, K>())) void k_outer(KArgs a) {
+template <typename T, int D, int S, int K, int M, bool kFew>
+__global__ __launch_bounds__(256, (outer_waves<T, K>(kFew))) void k_outer(KArgs a) {
   extern __shared__ char smem_raw[];
   const int n_dir_o = a.lv0.n_dir;
   const int64_t p = int64_t(blockIdx.x) / n_dir_o;
@@ -676,7 +682,7 @@ __global__ __launch_bounds__(256, (outer_waves<T, D, S, K>())) void k_outer(KArg
     if (threadIdx.x == 0) *out = OuterRes<T>{w1f, 0, 0, 0};
     return;
   }
-  outer_line<T, D, S, K, M>(a, p, mo, a.lv0, a.lv1, w1f, out, smem_raw);
+  outer_line<T, D, S, K, M, !(kFew && sizeof(T) == 4)>(a, p, mo, a.lv0, a.lv1, w1f, out, smem_raw);
 }
 
 // Two-level result of point p from its outer-line results res[0 .. n_dir_o):
@@ -805,7 +811,11 @@ hipError_t launch_T(const KArgs& a, int depth, hipStream_t st, KTimer* tm) {
   size_t lds = outer_lds_bytes<T>(a.lv0, a.lv1, M);
   dim3 grd_o(unsigned(a.n * a.lv0.n_dir));
   if (tm) tm->begin("outer", st);
-  hipLaunchKernelGGL((k_outer<T, D, S, K, M>), grd_o, blk, lds, st, a);
+  constexpr bool has_few = outer_waves<T, K>(true) < outer_waves<T, K>(false);
+  if (has_few && a.n * a.lv0.n_dir <= kFewBlocks)
+    hipLaunchKernelGGL((k_outer<T, D, S, K, M, has_few>), grd_o, blk, lds, st, a);
+  else
+    hipLaunchKernelGGL((k_outer<T, D, S, K, M, false>), grd_o, blk, lds, st, a);
   if (tm) tm->end(st);
   if (tm) tm->begin("finalize", st);
   hipLaunchKernelGGL((k_finalize<T, D, S, K, M>), grd, blk, 0, st, a);

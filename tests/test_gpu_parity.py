@@ -376,3 +376,37 @@ def test_fp64_results_scale_with_the_moduli(lib, dim, dirs):
     assert np.array_equal(a["tree"], b["tree"])
     assert np.array_equal(a["flags"], b["flags"]), int((a["flags"] != b["flags"]).sum())
     assert (a["flags"] & 16).sum() >= 16 * 20 and (a["flags"] & 16 == 0).sum() >= 20
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,model,inner,mat,beta_max", [
+    (2, 0, (8, 8, 65), {}, 0.5),
+    (2, 0, (8, 8, 65), dict(D_inf=0.9, D0=0.3, lam=0.5), 0.0),
+    (2, 0, (8, 4, 257), dict(D_inf=0.5, D0=2.0, lam=40.0), 0.1),
+    (2, 0, (8, 8, 129), dict(D_inf=0.999, D0=0.02, mu=5.0), 3.0),
+    (3, 0, (9, 8, 65), {}, 0.5),
+    (3, 0, (8, 4, 257), dict(D_inf=0.6, D0=0.5), 0.05),
+    (2, 2, (4, 4, 33), {}, 0.5),
+    (3, 2, (4, 4, 257), {}, 0.5),
+    (2, 1, (4, 4, 65), {}, 0.0),
+])
+def test_few_and_many_outer_lines_give_the_same_bits(lib, kind, dim, model, inner, mat, beta_max):
+    """Two levels with 512 outer lines (held to two waves a SIMD; FP32 samples every inner
+    line) and with 528 (three waves; inner neo-Hooke lines whose centre is shown to be a hull
+    vertex are left out): the same values, stresses, trees and flags, bit for bit, and the
+    oracle's energies."""
+    r1, h, torch = lib
+    cfg = WL.small_random(dim, 33, (4, 4), 33, tau=1.2, depth=2, inner=inner, sigma=0.3 if dim == 2 else 0.2,
+                          beta_max=beta_max, seed_tag=970 + dim)
+    cfg["material"].update(mat)
+    if model == 0:        # more wave steps than proves_lines asks for, in both types
+        lanes = h.inner_segment_width(inner[2], r1.R1_F32 if kind == "f32" else r1.R1_F64, dim)
+        assert inner[0] * inner[1] > 4 * (64 // lanes)
+    many = run_gpu(lib, cfg, kind, model=model)
+    few = run_gpu(lib, dict(cfg, F=cfg["F"][:, :32].copy(), beta_n=cfg["beta_n"][:32].copy()), kind, model=model)
+    for k in ("W", "P", "flags", "tree"):
+        c = many[k][:, :32] if k == "P" else many[k][:32]
+        assert np.array_equal(few[k], c, equal_nan=k in ("W", "P")), (k, int((few[k] != c).sum()))
+    some = slice(0, 33, 8)
+    _, _, W, _, _ = run_oracle(cfg, many["F_in"][:, some].copy(), many["bn_in"][some].copy(), model, want_tree=False)
+    assert PA.energy_errors(many["W"][some], W, kind).max() <= PA.RTOL[kind]
