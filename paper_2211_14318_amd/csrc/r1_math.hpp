@@ -16,11 +16,13 @@
 //           e^r by its Taylor polynomial of degree 13 (truncation below 2^-57),
 //           then 2^k by ldexp.
 //
-// The reduction's quotient is the correctly rounded one on both sides: an IEEE
-// division on the host, and on the device the hardware reciprocal (2^-23 at worst)
-// with one Newton step (2^-46) and Markstein's residual correction, whose error
-// before the last rounding is the square of that -- no scaling, since the operands'
-// exponents need none.
+// The reduction's quotient is an IEEE division on the host; on the device it is the
+// hardware reciprocal (2^-23 at worst) with one Newton step (2^-46) and a residual
+// correction, whose error before the last rounding is the square of that: the correctly
+// rounded quotient but where that lies within 2^-39 of a unit in the last place of the
+// midpoint of two numbers, and then possibly the other of the two -- no scaling, since the
+// operands' exponents need none.  (R1X_RCP_SEED: a host function in the place of the
+// hardware reciprocal, for checks of the device's steps.)
 //
 // log_f64 and exp_f64 follow the C library on special values: log of 0 is -inf, of
 // a negative number or NaN is NaN, of +inf is +inf; exp of -inf (and below -746) is
@@ -44,8 +46,12 @@ constexpr double kLog2e = 0x1.71547652b82fep+0;
 
 // n / d for d in [1, 4) and |n| < 1 either 0 or at least 2^-60.
 __host__ __device__ inline double near_one_quotient(double n, double d) {
+#if defined(__HIP_DEVICE_COMPILE__) || defined(R1X_RCP_SEED)
 #if defined(__HIP_DEVICE_COMPILE__)
   double y = __builtin_amdgcn_rcp(d);
+#else
+  double y = R1X_RCP_SEED(d);
+#endif
   y = std::fma(std::fma(-d, y, 1.0), y, y);
   const double q = n * y;
   return std::fma(std::fma(-d, q, n), y, q);

@@ -105,6 +105,23 @@ def test_fp64_log_exp_accuracy(tmp_path):
     assert max(worst.values()) <= 1.5, worst
 
 
+def test_fp64_device_steps_stay_within_their_bounds(tmp_path):
+    """The device's form of the FP64 sampling functions with any reciprocal estimate within
+    2^-23 (tests/math_f64_steps_check.cpp): the quotient is within 2^-39 of a unit of the last
+    place of a correct rounding (plus 2^-11, what the x87 quotient it is compared with is
+    rounded to), log and exp within the 1.5 units of their host form."""
+    import subprocess
+    exe = tmp_path / "math_steps_check"
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-Wall", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "paper_2211_14318_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "math_f64_steps_check.cpp"), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout
+    worst = {l.split()[1]: float(l.split()[2]) for l in out.splitlines() if l.startswith("max_ulp")}
+    assert len(worst) == 8 and out.strip().splitlines()[-1] == "ok", out
+    assert max(v for k, v in worst.items() if k.startswith("quotient")) <= 0.5 + 2.0 ** -11 + 2.0 ** -39, worst
+    assert max(v for k, v in worst.items() if not k.startswith("quotient")) <= 1.5, worst
+
+
 def build_grid_check(exe, extra_flags=()):
     import subprocess
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wno-unknown-pragmas", "-D__HIP_PLATFORM_AMD__",
