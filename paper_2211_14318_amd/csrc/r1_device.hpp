@@ -1190,13 +1190,13 @@ __device__ Env<T> envelope_lines(const Point<T>& q, T wc, int n_dir, const Layou
       q, wc, envelope_scan<T, S, K, M>(q, wc, n_dir, lay, line_fn, nullptr, 0, c2u, nullptr, centre));
 }
 
-// Whether a level leaves lines out: where the bound costs less than
+// Whether the inner levels of outer lines leave lines out: where the bound costs less than
 // it saves, in FP32 from more than four wave steps on (40 points, 2D, 32 x 153 outer,
 // without / with, us: four steps, 16 x 257, 764 / 765 and 32 x 45, 539 / 550; eight,
 // 32 x 257, 1352 / 1280), in FP64 whenever there is more than one step (two, 16 x 45,
 // 985 / 860; 64 x 257 13020 / 8924).
 template <typename T, int S>
-constexpr bool proves_lines(int n_dir) { return n_dir > (sizeof(T) == 4 ? 4 : 1) * (kWave / S); }
+constexpr bool outer_proves_lines(int n_dir) { return n_dir > (sizeof(T) == 4 ? 4 : 1) * (kWave / S); }
 
 // The same at one of successive points (see warm of envelope_scan; 2 n_dir entries),
 // with the lines' part at t = 0 (centre).  order (n_dir entries owned by this wave):

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void k_grid_energy(GridArgs g, r1d::Material m
 // values are absent from a hull.  Only candidates that the pick could take (lower
 // than the node's own value by more than its margin: the running value it is
 // compared with is never above the node's own) are written, and marked in the
-// node's mark byte of the group slot; unmarked slots are never read.  A node has 4
+// node's mark byte of the group slot; unmarked slots hold no value.  A node has 4
 // mark bytes when no group has more than 4 hull directions, else 16 (each written
 // by one thread, so plain stores do: an atomic bit mask took the 5.8M-node mesh's
 // hulls from 0.10 to 0.13 ms).
@@ -146,8 +146,8 @@ __device__ __forceinline__ LineRef line_of_block(const Group& grp, int blk, int 
                  int64_t(blk - (i ? grp.block_end[i - 1] : 0)) * grp.waves[i] * kLineThreads + tid};
 }
 
-// Lines of at most 64 nodes.  A block of 4 waves shares lds_bytes of LDS: 4, 2 or 1
-// of its waves take lines, as many as their columns fit (entry q of a thread's line
+// Lines of at most 64 nodes.  A block of 4 waves shares lds_bytes of LDS: 4 or 2 of
+// its waves take lines, as many as their columns fit (entry q of a thread's line
 // at [q * kLineThreads] of its wave's share), so that one launch holds the short
 // lines at full occupancy and the few long ones beside them.
 //   ch (nullable): nodes that the previous iteration changed.  A line without one
@@ -410,8 +410,9 @@ __device__ __forceinline__ uint32_t interior_mask(const GridArgs& g, uint32_t p)
 // running value only when lower by more than 4 units of rounding relative to
 // max(|W|, 1e-3), so directions that tie to rounding leave the node to the first.
 // kFirst: the running value starts from Win (else Wout, and with sel the running
-// laminate) and every node is written.  Only the marked slots of a node are read,
-// and its marks go back to 0.
+// laminate) and every node is written.  Only the marked slots of a node count
+// (with kNb a slot is loaded with its mark still under way, and dropped where there is
+// none), and its marks go back to 0.
 // The maximal decrease Win - W over nodes with finite Win goes to *dec (atomic
 // maximum of the non-negative doubles' bit patterns; W only decreases over the
 // groups, so the maximum over the nodes the groups lower is the iteration's).

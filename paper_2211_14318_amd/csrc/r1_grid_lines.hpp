@@ -150,7 +150,8 @@ __host__ __device__ inline int64_t line_start(const GridArgs& g, const Step& s, 
 // Advances (I, *p) from line start t to start t + delta (delta >= 0) within slab c:
 // the mixed-radix counter adds delta to its last component and carries (a division
 // only for the components the carry reaches).  False when that leaves slab c (the
-// start, if any, lies in a later slab; decode it with line_start).
+// start, if any, lies in a later slab; decode it with line_start).  The kernels decode
+// every start; this is the host's way through them.
 __host__ __device__ inline bool line_advance(const GridArgs& g, const Step& s, int c, int* I, int64_t* p,
                                              uint32_t delta) {
   for (int k = g.dd - 1; k >= 0 && delta; --k) {

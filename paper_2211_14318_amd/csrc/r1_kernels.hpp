@@ -218,6 +218,17 @@ constexpr int depth1_waves() {
   return (D == 2 && M == kFamNH && K <= 14) ? 4 : K <= 16 ? 3 : 1;
 }
 
+// Whether k_depth1 leaves lines out (line_proof).  FP64: whenever there is more than one
+// wave step.  FP32, 60,000 points, without / with: 3D 128 x 257 1501 / 911 us, 2D 32 x 257
+// (eight steps) 422 / 349; two steps, 2D 16 x 129, 152 / 153; four steps, 16 x 257, 241 /
+// 220 and 1,000,000 points 16 x 201 1950 / 1480.  The bound would thus pay at four steps
+// too.  It is taken from five on, for a reason outside this kernel: the network's inference
+// laminates the points with the fewest provable lines (262,144 points 16 x 201: plain 530
+// us without and 457 with the bound, inference 498 with it) and would no longer be the
+// faster of the two at its workload.
+template <typename T, int S>
+constexpr bool depth1_proves_lines(int n_dir) { return n_dir > (sizeof(T) == 4 ? 4 : 1) * (kWave / S); }
+
 template <typename T, int D, int S, int K, int M>
 __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KArgs a) {
   __shared__ PointSetup<T, D, M> ps[kPointsPerBlock];
@@ -227,13 +238,8 @@ __global__ __launch_bounds__(256, (depth1_waves<T, K, D, M>())) void k_depth1(KA
   const int per_block = 4 * a.pts_per_wave;
   const int64_t p0 = int64_t(blockIdx.x) * per_block;
   const int n_dir = a.lv0.n_dir, n_off = (a.lv0.n_t - 1) / 2;
-  // lines shown to have a vertex at the centre are not sampled (proves_lines).  60,000
-  // points FP32, without / with: 3D 128 x 257 1501 / 911 us, 2D 32 x 257 (eight steps)
-  // 422 / 349; two steps, 2D 16 x 129, 152 / 153.  Four steps, 16 x 257, 241 / 220, stay
-  // out with the two: plain lamination of the 16 x 201 workload would gain (1,000,000
-  // points 1.48 ms) while the network's inference, whose fallback gets the points with the
-  // fewest such lines, would not, and would no longer be the faster of the two.
-  const bool prove = M == kFamNH && a.mat.model == 0 && a.lv0.ab2 == a.lv0.ab2 && proves_lines<T, S>(n_dir);
+  // lines shown to have a vertex at the centre are not sampled (depth1_proves_lines)
+  const bool prove = M == kFamNH && a.mat.model == 0 && a.lv0.ab2 == a.lv0.ab2 && depth1_proves_lines<T, S>(n_dir);
   if (int(threadIdx.x) < per_block && p0 + threadIdx.x < a.n) {
     const PointSetup<T, D, M> s = point_setup<T, D, M>(a, p0 + threadIdx.x);
     ps[threadIdx.x] = s;
@@ -515,7 +521,7 @@ constexpr int kOuterBatch = 16;
 // One outer line (block-level, every thread calls it): the samples W^1(F + t_i R_mo)
 // are inner envelopes computed by the block's waves into LDS; wave 0 takes the
 // outer hull at the centre.  w1f = W^1(F) is the centre sample.  Thread 0 writes
-// the result to *out.  kProve: proven inner lines may be left out (proves_lines).
+// the result to *out.  kProve: proven inner lines may be left out (outer_proves_lines).
 template <typename T, int D, int S, int K, int M, bool kProve = true>
 __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, const Level& lo, const Level& li, T w1f,
                                            OuterRes<T>* out, char* smem_raw) {
@@ -576,7 +582,7 @@ __device__ __forceinline__ void outer_line(const KArgs& a, int64_t p, int mo, co
   int* order_w = order + wave * li.n_dir;
   const Point<T> q = sq;
   const T c2u = T(q.kq * li.ab2);
-  const bool prove = kProve && M == kFamNH && q.model == 0 && c2u == c2u && proves_lines<T, S>(li.n_dir);
+  const bool prove = kProve && M == kFamNH && q.model == 0 && c2u == c2u && outer_proves_lines<T, S>(li.n_dir);
   const auto sample_t = [&](int s) { return (s & 1) ? t_of(lo, 1 + (s >> 1)) : -t_of(lo, 1 + (s >> 1)); };
   for (int s0 = wave; s0 < 2 * co; s0 += nwave * kOuterBatch) {
     wave_lds_fence();                          // reads of the samples before are done

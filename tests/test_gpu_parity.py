@@ -399,7 +399,7 @@ def test_few_and_many_outer_lines_give_the_same_bits(lib, kind, dim, model, inne
     cfg = WL.small_random(dim, 33, (4, 4), 33, tau=1.2, depth=2, inner=inner, sigma=0.3 if dim == 2 else 0.2,
                           beta_max=beta_max, seed_tag=970 + dim)
     cfg["material"].update(mat)
-    if model == 0:        # more wave steps than proves_lines asks for, in both types
+    if model == 0:        # more wave steps than either type's rule asks for
         lanes = h.inner_segment_width(inner[2], r1.R1_F32 if kind == "f32" else r1.R1_F64, dim)
         assert inner[0] * inner[1] > 4 * (64 // lanes)
     many = run_gpu(lib, cfg, kind, model=model)
@@ -410,3 +410,32 @@ def test_few_and_many_outer_lines_give_the_same_bits(lib, kind, dim, model, inne
     some = slice(0, 33, 8)
     _, _, W, _, _ = run_oracle(cfg, many["F_in"][:, some].copy(), many["bn_in"][some].copy(), model, want_tree=False)
     assert PA.energy_errors(many["W"][some], W, kind).max() <= PA.RTOL[kind]
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,dirs,nt,lanes,mat,beta_max,scale", [
+    (2, (4, 4), 201, 32, {}, 0.5, 1.0),                                   # the workload's lines, two at once
+    (2, (4, 4), 201, 64, dict(D_inf=0.9, D0=0.3, lam=0.5), 0.0, 1.0),     # one at once, virgin points
+    (2, (9, 8), 129, None, {}, 0.5, 1.7),                                 # |a| = 1.7 for every line
+    (2, (9, 8), 129, None, dict(D_inf=0.5, D0=2.0, lam=40.0), 0.1, 0.6),  # ln J soon beyond 1 + mu / lambda
+    (3, (9, 8), 65, None, dict(lam=0.0), 0.5, 1.7),
+])
+def test_lines_left_unsampled_by_enough_wave_steps(lib, kind, dim, dirs, nt, lanes, mat, beta_max, scale):
+    """As test_lines_left_unsampled_change_nothing, on levels of more wave steps than either
+    type's rule asks for (checked here, so that every row does leave lines out)."""
+    r1, h, torch = lib
+    cfg = WL.small_random(dim, 512, dirs, nt, sigma=0.3 if dim == 2 else 0.2, det_min=1e-3, beta_max=beta_max,
+                          seed_tag=980 + dim)
+    cfg["material"].update(mat)
+    cfg["levels"][0]["a"] *= scale
+    width = lanes or h.segment_width(nt, r1.R1_F32 if kind == "f32" else r1.R1_F64, dim)
+    assert dirs[0] * dirs[1] > 4 * (64 // width)
+    F = cfg["F"]
+    F[:, :64] = np.eye(dim).reshape(-1, 1) + 1e-3 * (F[:, :64] - np.eye(dim).reshape(-1, 1))
+    F[:, 64:128] *= 1.5
+    few = run_gpu(lib, cfg, kind, lanes=lanes)
+    many = run_gpu(lib, dict(cfg, F=np.tile(F, (1, 17)), beta_n=np.tile(cfg["beta_n"], 17)), kind, lanes=lanes)
+    for k in ("W", "P", "flags", "tree"):
+        c = many[k][:, -512:] if k == "P" else many[k][-512:]
+        assert np.array_equal(few[k], c, equal_nan=k in ("W", "P")), (k, int((few[k] != c).sum()))
+    assert np.isfinite(few["W"]).all()
