@@ -457,24 +457,29 @@ __device__ __forceinline__ long long list_entry(const PickDir& d) {
 }
 
 // lists[M * pitch ..]: the entries of dirs that a node with interior mask M looks
-// at, in order, filled up to a multiple of kPickBatch with steps of 0 and no slot, which
-// hold no candidate; counts[M] their number.  One wave per mask.
+// at, in order, filled up to a multiple of kPickBatch with the last of them (whose
+// candidate, once taken, does not lie below the value it gave; a step of 0 would make the
+// node its own neighbour, whose midpoint is -inf where the node's double overflows);
+// counts[M] their number.  One wave per mask.
 __global__ __launch_bounds__(64) void k_grid_lists(const PickDir* __restrict__ dirs, int ne, int pitch,
                                                    long long* __restrict__ lists, int* __restrict__ counts) {
   const uint32_t M = blockIdx.x;
   const int lane = threadIdx.x;
   long long* const list = lists + int64_t(M) * pitch;
   int at = 0;
+  long long last = 0;
   for (int e0 = 0; e0 < ne; e0 += 64) {
     const int e = e0 + lane;
     const PickDir d = dirs[e < ne ? e : 0];
     const bool v = e < ne && (d.slot >= 0 || (d.need & ~M) == 0u);
     const unsigned long long b = __ballot(v);
-    if (v) list[at + __popcll(b & ((1ull << lane) - 1ull))] = list_entry(d);
+    const long long entry = list_entry(d);
+    if (v) list[at + __popcll(b & ((1ull << lane) - 1ull))] = entry;
+    if (b) last = __shfl(entry, 63 - __builtin_clzll(b), 64);
     at += __popcll(b);
   }
   const int full = (at + kPickBatch - 1) / kPickBatch * kPickBatch;
-  if (at + lane < full) list[at + lane] = 0;
+  if (at + lane < full) list[at + lane] = last;
   if (lane == 0) counts[M] = full;
 }
 
@@ -559,9 +564,8 @@ __global__ __launch_bounds__(256) void k_grid_pick(GridArgs g, Guard guard, int 
           const uint32_t code = uint32_t(e[j] >> 32), slot1 = code & 31u;
           // the monotone chain on three nodes: the middle one is popped exactly when
           // it lies on or above the chord, and its candidate is the chord's midpoint
-          // (an absent neighbour, +inf or NaN, fails the comparisons; a filling entry has
-          // none: the midpoint of w0 and w0 is -inf where their sum overflows)
-          const bool cut = int32_t(e[j]) != 0 && w0 - a[j] >= b[j] - w0;
+          // (an absent neighbour, +inf or NaN, fails the comparisons)
+          const bool cut = w0 - a[j] >= b[j] - w0;
           const bool ok = slot1 ? ((mk >> (slot1 - 1u)) & 1u) != 0u : cut;
           const T c = slot1 ? a[j] : (a[j] + b[j]) / T(2);
           if (ok && c < lim) take(c, int(code >> 5), int(slot1) - 1);
