@@ -699,8 +699,8 @@ __device__ __forceinline__ void slope_bridge(const T (&w)[K], const Layout<T, S,
 //
 // thr: a line whose hull value at the centre is shown to exceed it may return
 // an upper bound above thr instead (see slope_bridge); +inf: exact for every
-// line.  cap: lowered to a value that the line's hull value is not below where its
-// search ends at the iteration cap (h is then an upper bound only).
+// line.  cap: lowered, where the line's search ends at the iteration cap (h is then an
+// upper bound only), to a value that its hull value is not below, and to top at most.
 //
 // hot (wave-uniform): every line of the wave has a warm start.  The vertex
 // test is then skipped: the centre is a vertex exactly when the bridge of the
@@ -709,7 +709,7 @@ __device__ __forceinline__ void slope_bridge(const T (&w)[K], const Layout<T, S,
 // standard path instead.
 template <typename T, int S, int K>
 __device__ __forceinline__ LineHull<T> hull_centre(const T (&w)[K], T wc, const T (&wci)[K / 2],
-                                                   const Layout<T, S, K>& lay, T& sig, bool hot, T thr, T& cap) {
+                                                   const Layout<T, S, K>& lay, T& sig, bool hot, T thr, T top, T& cap) {
   constexpr int H = K / 2;
   LineHull<T> r;
   r.h = wc; r.mp = 0; r.mq = 0;
@@ -764,7 +764,7 @@ __device__ __forceinline__ LineHull<T> hull_centre(const T (&w)[K], T wc, const 
     T wp = T(0), wq = T(0);
     // the last pass bounds the hull value from below; its slope is by then within rounding
     // of the best one where the alternating search does not end either
-    const T low = fmin(fmin(ep, eq), wc);
+    const T low = fmin(fmin(fmin(ep, eq), wc), top);
     int capped = 0;
     bridge_alternating<T, S, K>(w, wci, lay, todo, mp, wp, mq, wq, capped);
     if (capped) cap = fmin(cap, low);
@@ -1139,7 +1139,8 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
       sg = s2 == s2 ? fma(T(2), s1, -s2) : s1;
     }
     const bool hot = warm && __all(act && s1 == s1);
-    LineHull<T> lh = hull_centre<T, S, K>(w, wcs, wci, lay, sg, hot, thr, best.cap);
+    // (a warm search is never stopped early: every one that is capped is reported)
+    LineHull<T> lh = hull_centre<T, S, K>(w, wcs, wci, lay, sg, hot, thr, warm ? -inf_v<T>() : inf_v<T>(), best.cap);
     if (warm && act && (lane & (S - 1)) == 0) {
       warm[n_warm + dir] = sg == sg ? s1 : sg;
       warm[dir] = sg;
@@ -1153,8 +1154,6 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
       }
     }
   }
-  // a warm search is never stopped early: every one that is capped is reported
-  if (warm && best.cap < inf_v<T>()) best.cap = -inf_v<T>();
   // across segments: lexicographic (value, direction)
 #pragma unroll
   for (int off = S; off < kWave; off <<= 1) {
