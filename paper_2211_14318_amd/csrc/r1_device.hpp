@@ -1082,6 +1082,16 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
   T wci[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) wci[h] = wcs * lay.inv_m[h];
+  // The early stop's margin (below) is at least eight units of rounding of the hull form,
+  // beside whose values the tie margin may be small (D0 well above mu): the bounds and
+  // chords of lines that tie differ by a few, and which of them is met first depends on the
+  // split over waves.  FP32 has them in the margin's floor, once per point (the hull's value
+  // lies between those of W = 0 and of the centre; 2D 16 x 201 lines 2% slower, others the
+  // same), FP64 on the threshold.
+  constexpr T ulps = sizeof(T) == 4 ? T(8 * 1.1920929e-7) : T(8 * 2.220446049250313e-16);
+  T floor = tie_floor<T>();
+  if (sizeof(T) == 4 && !warm && scaled)
+    floor = fmax(floor, ulps / (T(2) * tie_margin<T>()) * fmax(fabs(wcs * q.sc), fabs(q.B)));
   Env<T> best = seg == 0 ? seed : env_none<T>();
   for (int m0 = from; m0 < n; m0 += step) {
     const bool act = m0 + seg < n;
@@ -1127,8 +1137,9 @@ __device__ Env<T> envelope_scan(const Point<T>& q, T wc, int n, const Layout<T, 
       for (int off = S; off < kWave; off <<= 1) bw = fmin(bw, __shfl_xor(bw, off, kWave));
       if (bw < inf_v<T>()) {
         const T bW = scaled ? fma(bw, q.sc, q.B) : bw;
-        const T mW = T(2) * tie_margin<T>() * fmax(fabs(bW), tie_floor<T>());
+        const T mW = T(2) * tie_margin<T>() * fmax(fabs(bW), floor);
         thr = bw + (scaled ? mW * rcp_t(q.sc) : mW);
+        if (sizeof(T) == 8) thr = fma(fabs(thr), ulps, thr);
       }
     }
     T sg = T(__builtin_nan("")), s1 = sg;

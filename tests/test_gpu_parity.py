@@ -439,3 +439,27 @@ def test_lines_left_unsampled_by_enough_wave_steps(lib, kind, dim, dirs, nt, lan
         c = many[k][:, -512:] if k == "P" else many[k][-512:]
         assert np.array_equal(few[k], c, equal_nan=k in ("W", "P")), (k, int((few[k] != c).sum()))
     assert np.isfinite(few["W"]).all()
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,nt,sigma,beta_max", [(3, 1101, 1e-3, 0.0), (2, 1101, 0.05, 0.0), (2, 405, 0.3, 3.0)])
+def test_tie_flag_does_not_depend_on_the_batch(lib, kind, dim, nt, sigma, beta_max):
+    """D0 = 25 mu: the energies are small beside the hull form's values, whose rounding then
+    exceeds the tie margin in FP32.  A small batch (several waves per point) and a large one
+    report the same flags, and flag the points whose two best directions, laminated one by
+    one, have the same energy."""
+    cfg = WL.small_random(dim, 400, (8, 8), nt, tau=0.05, sigma=sigma, beta_max=1.0, seed_tag=990 + dim)
+    cfg["material"].update(mu=1.0, lam=0.05, D_inf=0.9, D0=25.0)
+    cfg["beta_n"] *= beta_max
+    few = run_gpu(lib, cfg, kind)
+    many = run_gpu(lib, dict(cfg, F=np.tile(cfg["F"], (1, 22)), beta_n=np.tile(cfg["beta_n"], 22)), kind)
+    for k in ("W", "P", "flags", "tree"):
+        c = many[k][:, -400:] if k == "P" else many[k][-400:]
+        assert np.array_equal(few[k], c), (k, int((few[k] != c).sum()))
+    one = []
+    for a, b in zip(cfg["levels"][0]["a"], cfg["levels"][0]["b"]):
+        one.append(run_gpu(lib, dict(cfg, levels=[WL.level(a[None], b[None], nt, 0.05)]), kind)["W"])
+    best = np.sort(np.array(one), axis=0)[:2]
+    tied = (best[0] == best[1]) & (few["tree"][:, 0, 1] != (nt - 1) // 2)
+    assert np.array_equal(best[0], few["W"])
+    assert (few["flags"][tied] & 16 != 0).all() and (kind == "f64" or tied.sum() > 100)
