@@ -37,7 +37,7 @@ __device__ __forceinline__ float sample_at(float t, const r1d::Line<float>& L, c
 template <typename T, int D, int M>
 __device__ __forceinline__ bool chord_below(const CheckArgs& a, const r1d::Point<float>& q, const double* G,
                                             const double* cof, float target, int m) {
-  const r1d::Line<float> L = r1d::line_setup<float, D, M>(q, G, cof, a.lv.a + m * D, a.lv.b + m * D);
+  const r1d::Line<float> L = r1d::line_setup<float, D, M, false>(q, G, cof, a.lv.a + m * D, a.lv.b + m * D);
   float lo = __builtin_inff(), hi = __builtin_inff();
   for (int k = 0; k < a.n_off; ++k) {
     const float to = a.toff[k];

@@ -214,13 +214,23 @@ __device__ __forceinline__ double det_of(const double* G, const double* cof) {
 // Coefficients are formed in double and scaled by k.
 // Per-point part of the St. Venant-Kirchhoff line coefficients: G, E0, G E0,
 // tr E0 and E0:E0 (shared by every line through the point).
+// kFused: multiplications and additions are fused as written here (mad).  Left to the code
+// generator (the mesh's node energies, the network's energies), which of two products is
+// fused depends on the kernel around it; the lamination of small and of large batches,
+// which two kernels do, then differed in the last bit of the FP64 energies.
+template <bool kFused>
+__device__ __forceinline__ double mad(double x, double y, double z) {
+  if constexpr (kFused) return fma(x, y, z);
+  return z + x * y;
+}
+
 template <int D>
 struct StvkGeom {
   double G[D * D], E0[D * D], GE0[D * D];
   double e0, ee;
 };
 
-template <int D>
+template <int D, bool kFused = true>
 __device__ __forceinline__ StvkGeom<D> make_stvk_geom(const double* G) {
   StvkGeom<D> g;
   g.e0 = 0.0;
@@ -233,26 +243,26 @@ __device__ __forceinline__ StvkGeom<D> make_stvk_geom(const double* G) {
     for (int j = 0; j < D; ++j) {
       double c = 0.0;
 #pragma unroll
-      for (int r = 0; r < D; ++r) c += G[r * D + i] * G[r * D + j];
+      for (int r = 0; r < D; ++r) c = mad<kFused>(G[r * D + i], G[r * D + j], c);
       g.E0[i * D + j] = 0.5 * (c - (i == j ? 1.0 : 0.0));
     }
 #pragma unroll
   for (int i = 0; i < D; ++i) g.e0 += g.E0[i * D + i];
 #pragma unroll
-  for (int i = 0; i < D * D; ++i) g.ee += g.E0[i] * g.E0[i];
+  for (int i = 0; i < D * D; ++i) g.ee = mad<kFused>(g.E0[i], g.E0[i], g.ee);
 #pragma unroll
   for (int i = 0; i < D; ++i)
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       double c = 0.0;
 #pragma unroll
-      for (int r = 0; r < D; ++r) c += G[i * D + r] * g.E0[r * D + j];
+      for (int r = 0; r < D; ++r) c = mad<kFused>(G[i * D + r], g.E0[r * D + j], c);
       g.GE0[i * D + j] = c;
     }
   return g;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kFused = true>
 __device__ __forceinline__ Line<T> stvk_line_g(double lam, double mu, double k, const StvkGeom<D>& g,
                                                const double* a, const double* b) {
   double e1 = 0.0, ge0b = 0.0, beb = 0.0, gta2 = 0.0, aa = 0.0, bb = 0.0;
@@ -261,39 +271,45 @@ __device__ __forceinline__ Line<T> stvk_line_g(double lam, double mu, double k, 
     double gta = 0.0, e0b = 0.0, ge = 0.0;
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      gta += g.G[i * D + j] * a[i];
-      e0b += g.E0[j * D + i] * b[i];
-      ge += g.GE0[i * D + j] * a[i];
+      gta = mad<kFused>(g.G[i * D + j], a[i], gta);
+      e0b = mad<kFused>(g.E0[j * D + i], b[i], e0b);
+      ge = mad<kFused>(g.GE0[i * D + j], a[i], ge);
     }
-    e1 += gta * b[j];
-    ge0b += ge * b[j];
-    beb += b[j] * e0b;
-    gta2 += gta * gta;
-    aa += a[j] * a[j];
-    bb += b[j] * b[j];
+    e1 = mad<kFused>(gta, b[j], e1);
+    ge0b = mad<kFused>(ge, b[j], ge0b);
+    beb = mad<kFused>(b[j], e0b, beb);
+    gta2 = mad<kFused>(gta, gta, gta2);
+    aa = mad<kFused>(a[j], a[j], aa);
+    bb = mad<kFused>(b[j], b[j], bb);
   }
   const double e0 = g.e0, e2 = 0.5 * aa * bb;
   Line<T> L;
   L.J0 = T(0);
   L.J1 = T(0);
-  L.c0 = T(k * (0.5 * lam * e0 * e0 + mu * g.ee));
-  L.c1 = T(k * (lam * e0 * e1 + 2.0 * mu * ge0b));
-  L.c2 = T(k * (0.5 * lam * (e1 * e1 + 2.0 * e0 * e2) + mu * (0.5 * gta2 * bb + 0.5 * e1 * e1 + aa * beb)));
+  if constexpr (kFused) {
+    L.c0 = T(k * fma(mu, g.ee, 0.5 * lam * e0 * e0));
+    L.c1 = T(k * fma(2.0 * mu, ge0b, lam * e0 * e1));
+    L.c2 = T(k * fma(0.5 * lam, fma(e1, e1, 2.0 * e0 * e2), mu * fma(aa, beb, fma(0.5 * e1, e1, 0.5 * gta2 * bb))));
+  } else {
+    L.c0 = T(k * (0.5 * lam * e0 * e0 + mu * g.ee));
+    L.c1 = T(k * (lam * e0 * e1 + 2.0 * mu * ge0b));
+    L.c2 = T(k * (0.5 * lam * (e1 * e1 + 2.0 * e0 * e2) + mu * (0.5 * gta2 * bb + 0.5 * e1 * e1 + aa * beb)));
+  }
   L.c3 = T(k * ((lam + 2.0 * mu) * e1 * e2));
   L.c4 = T(k * ((0.5 * lam + mu) * e2 * e2));
   return L;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kFused = true>
 __device__ __forceinline__ Line<T> stvk_line(double lam, double mu, double k, const double* G, const double* a,
                                              const double* b) {
-  return stvk_line_g<T, D>(lam, mu, k, make_stvk_geom<D>(G), a, b);
+  return stvk_line_g<T, D, kFused>(lam, mu, k, make_stvk_geom<D, kFused>(G), a, b);
 }
 
-template <typename T, int D, int M = kFamNH>
+template <typename T, int D, int M = kFamNH, bool kFused = true>
 __device__ __forceinline__ Line<T> line_setup(const Point<T>& q, const double* G, const double* cof,
                                               const double* a, const double* b) {
-  if constexpr (M == kFamSTVK) return stvk_line<T, D>(q.lam, q.mu, q.kq, G, a, b);
+  if constexpr (M == kFamSTVK) return stvk_line<T, D, kFused>(q.lam, q.mu, q.kq, G, a, b);
   const int model = q.model;
   const double kq = q.kq;
   Line<T> L;
@@ -378,10 +394,10 @@ __device__ __forceinline__ T w_sample_doublewell(T t, const Line<T>& L) {
 // W at a point (the centre sample of every line through it), in the path's precision,
 // through the hull form for the damage energies (the value the envelope returns
 // where the point does not laminate).
-template <typename T, int D, int M = kFamNH>
+template <typename T, int D, int M = kFamNH, bool kFused = true>
 __device__ __forceinline__ T w_point(const Point<T>& q, const double* G, const double* cof) {
   double a0[3] = {0, 0, 0};
-  Line<T> L = line_setup<T, D, M>(q, G, cof, a0, a0);
+  Line<T> L = line_setup<T, D, M, kFused>(q, G, cof, a0, a0);
   if constexpr (M == kFamSTVK) return fma(ws_sample_stvk<T>(T(0), L, q), q.sc, q.B);
   return q.model == 0 ? fma(ws_sample<T>(T(0), L, q), q.sc, q.B) : w_sample_doublewell<T>(T(0), L);
 }
@@ -389,7 +405,7 @@ __device__ __forceinline__ T w_point(const Point<T>& q, const double* G, const d
 // Same, for code whose model is known at run time only.
 template <typename T, int D>
 __device__ __forceinline__ T w_point_any(const Point<T>& q, const double* G, const double* cof) {
-  return q.model == 2 ? w_point<T, D, kFamSTVK>(q, G, cof) : w_point<T, D, kFamNH>(q, G, cof);
+  return q.model == 2 ? w_point<T, D, kFamSTVK, false>(q, G, cof) : w_point<T, D, kFamNH, false>(q, G, cof);
 }
 
 // ---- segment reductions ------------------------------------------------------

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256, 2) void k_infer(InferParams ip, const T* F, co
   const double raw = double(rawf);
   const bool convex = raw <= 0.0;
   r1d::Point<double> q = r1d::make_point<double, FAM>(ip.mat, b);
-  const double w_un = r1d::w_point<double, D, FAM>(q, G, cof);
+  const double w_un = r1d::w_point<double, D, FAM, false>(q, G, cof);
   const double wpred = convex ? w_un : w_un - raw;
   if (MODE == 1) {
     cal_bin[pt] = ok ? bin : -1;
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(512) void k_infer_lds(InferParams ip, const T* F, c
     if (MODE == 1) {
       if (valid && half == 0) {
         r1d::Point<double> q = r1d::make_point<double, FAM>(ip.mat, b);
-        const double w_un = r1d::w_point<double, D, FAM>(q, G, cof);
+        const double w_un = r1d::w_point<double, D, FAM, false>(q, G, cof);
         cal_bin[pt] = ok ? bin : -1;
         cal_w[pt] = float(convex ? w_un : w_un - raw);
         cal_gap[pt] = rawf;
@@ -444,7 +444,7 @@ __global__ __launch_bounds__(512) void k_infer_lds(InferParams ip, const T* F, c
     if (!valid || !ok) continue;
     if (half == 0) {
       r1d::Point<double> q = r1d::make_point<double, FAM>(ip.mat, b);
-      const double w_un = r1d::w_point<double, D, FAM>(q, G, cof);
+      const double w_un = r1d::w_point<double, D, FAM, false>(q, G, cof);
       W[pt] = T(convex ? w_un : w_un - raw);
       if (flags) flags[pt] = 0;
     } else {

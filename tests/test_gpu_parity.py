@@ -463,3 +463,20 @@ def test_tie_flag_does_not_depend_on_the_batch(lib, kind, dim, nt, sigma, beta_m
     tied = (best[0] == best[1]) & (few["tree"][:, 0, 1] != (nt - 1) // 2)
     assert np.array_equal(best[0], few["W"])
     assert (few["flags"][tied] & 16 != 0).all() and (kind == "f64" or tied.sum() > 100)
+
+
+@pytest.mark.parametrize("kind", ["f64", "f32"])
+@pytest.mark.parametrize("dim,dirs,nt,tau,mat", [(2, (8, 8), 201, 1.0, dict(mu=1.3, lam=0.7, D_inf=0.9, D0=0.3)),
+                                                 (2, (4, 4), 1219, 1.9, dict(mu=0.0991, lam=0.932, D_inf=0.9, D0=0.00211)),
+                                                 (3, (8, 8), 129, 1.0, dict(mu=2.24, lam=219.0, D_inf=0.3, D0=1.65))])
+def test_stvk_few_and_many_points_give_the_same_bits(lib, kind, dim, dirs, nt, tau, mat):
+    """St. Venant-Kirchhoff lines of |a| = 1.7 at 400 points and at 8800: the two kernels form
+    the same coefficients, so the same energies, stresses, trees and flags, bit for bit."""
+    cfg = WL.small_random(dim, 400, dirs, nt, tau=tau, sigma=0.3 if dim == 2 else 0.2, seed_tag=995 + dim)
+    cfg["material"].update(mat)
+    cfg["levels"][0]["a"] *= 1.7
+    few = run_gpu(lib, cfg, kind, model=2)
+    many = run_gpu(lib, dict(cfg, F=np.tile(cfg["F"], (1, 22)), beta_n=np.tile(cfg["beta_n"], 22)), kind, model=2)
+    for k in ("W", "P", "flags", "tree"):
+        c = many[k][:, -400:] if k == "P" else many[k][-400:]
+        assert np.array_equal(few[k], c), (k, int((few[k] != c).sum()))
